@@ -61,6 +61,8 @@ def algorithmic_bytes(kind: str, n: int, M: int, N: int, s: int) -> float:
     fwd_plane: read the stage input, write the spectrum.
     zderiv: read the spectrum, write its z derivative.
     couple: read the spectrum and the derivative, write the coupled spectrum.
+    stream: z derivative and coupling in one sweep (orders up to 7; 256^3 up
+    to 5): read the spectrum, write the coupled spectrum.
     inv_plane (grids up to 128, fused with the next stage's forward
     transform): read the coupled spectrum, the stage input, u and the
     per-degree loss maps ((N+1) n^3), write the stage output and its xy
@@ -73,7 +75,7 @@ def algorithmic_bytes(kind: str, n: int, M: int, N: int, s: int) -> float:
     F = M * n ** 3 * s
     if kind == "fwd_plane":
         return 2 * F
-    if kind == "zderiv":
+    if kind in ("zderiv", "stream"):
         return 2 * F
     if kind == "couple":
         return 3 * F
@@ -353,10 +355,10 @@ def expo_bench(a):
 def gmres_iteration_bytes(n, M, N, s, m, K):
     """Compulsory HBM bytes of one Arnoldi step averaged over a restart
     cycle of m steps. The operator: with K = 0 one application of S + Sigma
-    (forward plane pass 2F, z derivative 2F, coupling 3F, inverse pass
+    (forward plane pass 2F, streaming pass 2F, inverse pass
     reading the spectrum, input and loss maps and writing the output
     3F + maps); with K > 0 a copy (2F), K RK4 steps without bookkeeping (per
-    stage 2F + 2F + 3F and an inverse pass reading spectrum, stage input, u
+    stage 2F + 2F and an inverse pass reading spectrum, stage input, u
     and maps and writing 1: 4F + maps, the first stage reading u once: one F
     less) and the difference (3F). Then two classical Gram-Schmidt passes
     against j + 1 basis vectors (inner products read j + 2 vectors, the
@@ -365,9 +367,9 @@ def gmres_iteration_bytes(n, M, N, s, m, K):
     F = M * n ** 3 * s
     maps = (N + 1) * n ** 3 * s
     if K == 0:
-        op = 10 * F + maps
+        op = 7 * F + maps
     else:
-        op = 2 * F + K * (4 * (11 * F + maps) - F) + 3 * F
+        op = 2 * F + K * (4 * (8 * F + maps) - F) + 3 * F
     tot = 0.0
     for j in range(m):
         tot += op + 2 * ((j + 2) * F + (j + 3) * F) + 3 * F
@@ -842,6 +844,8 @@ def main():
     sbytes = 8 if wl.precision == "f64" else 4
 
     prof = s.profile_kernels(a.profile_steps)
+    if "zderiv" not in prof and "couple" in prof:
+        prof["stream"] = prof.pop("couple")   # one sweep does both
     per = {k: (t / c if c else 0.0) for k, (t, c) in prof.items()}
     dom = max((k for k in prof if k != "end_step"), key=lambda k: prof[k][0])
     alg = algorithmic_bytes(dom, wl.n, wl.M, wl.N, sbytes)

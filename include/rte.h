@@ -339,7 +339,8 @@ int rte_expo_advance(rte_handle* h, double t_ps);
 /* Run nsteps steps with plain launches, timing every kernel with HIP
  * events on the handle's stream, and store the summed milliseconds of each
  * kernel class in ms[0..12] and the launch counts in counts[0..12]. Classes:
- * 0 forward plane pass, 1 z-derivative pass, 2 moment coupling pass,
+ * 0 forward plane pass, 1 z-derivative pass, 2 moment coupling pass (with
+ * the z derivative in the same sweep where class 1 has no launch),
  * 3 inverse plane pass with epilogue, 4 end-of-step bookkeeping; on grids
  * split into row and pencil passes (n = 256): 5 forward row pass,
  * 6 forward y pencil pass, 7 inverse y pencil pass, 8 inverse row pass with

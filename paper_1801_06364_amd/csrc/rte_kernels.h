@@ -8,12 +8,16 @@
 // moments are mixed, which keeps every sweep over HBM coalesced:
 //   F  k_fwd_plane  per (moment, z-plane): x real-to-complex FFT and y FFT of
 //                   the plane in LDS -> xy spectrum S [b][z][ky][kx];
+//   W  k_stream     per (ky, a few kx columns, degree parity): z derivative
+//                   D = d/dz S (xy spectral, z physical) of every moment and
+//                   W = -i (kx Bx + ky By) S - Bz D in one sweep. Where its
+//                   accumulators exceed the registers (256^3 above P_5, P_21)
+//                   two passes do it:
 //   D  k_pencil     per (moment, ky, 16 kx columns): z FFT, times i k_z,
-//                   inverse z FFT -> D = d/dz S (xy spectral, z physical);
-//   C  k_couple     per spectral point, all moments in registers:
-//                   W = -i (kx Bx + ky By) S - Bz D, written over S
-//                   (k_couple_rt for orders beyond registers: a run-time
-//                   slot table, W to a separate buffer);
+//                   inverse z FFT -> D;
+//   C  k_couple     per spectral point, all moments in registers: W, written
+//                   over D (k_couple_rt for P_21: a run-time slot table, W to
+//                   a separate buffer);
 //   P  k_inv_plane  per (moment, z-plane): inverse y FFT, complex-to-real x
 //                   FFT and the fused pointwise epilogue (loss, in-scatter,
 //                   boundary layer, source, RK combine; after the last stage
@@ -86,6 +90,44 @@ template <int NN> struct GridC {
   static constexpr int H = NN / 2;
   static constexpr int E = elems_per_lane(NN);
   static_assert(elems_per_lane(NN / 2) == elems_per_lane(NN), "row/column lane shape");
+};
+
+// Layout of the xy spectra in HBM: [b][ky / KB][z][ky % KB][kx], kx < n/2.
+// KB = n (the rows of a z-plane together) leaves a z pencil of a few kx
+// columns in 64-byte pieces a whole plane apart: a copy kernel with the
+// streaming pass's accesses reaches 3.1 TB/s on the 537 MB spectrum of 128^3
+// P_7 FP32. With the rows of a few ky values of every z together (pieces of
+// 2 KB: KB = 4 FP32, 2 FP64) it reaches 4.8 TB/s (1 KB 5.1, 4 KB 3.5), and the
+// plane passes, which then move 2 KB pieces, keep their time if ZG = 8
+// z-planes of a moment run side by side (k_plane128: 575 us against 648 with
+// ZG = 1, 591 with 2, 572 with 16). The streaming pass itself: 333 -> 271 us
+// FP32, 647 -> 525 FP64. Smaller grids sit in the caches, and at 256^3 the
+// two y passes and the row pass lose what the streaming pass gains (per
+// stage 6.14 ms either way): KB = n there.
+template <typename T, int NN> struct SpecLayout {
+  static constexpr int H = NN / 2;
+  static constexpr int rows_for(int bytes) {   // ky rows per piece of about `bytes`
+    int k = 1;
+    while (2 * k * H * 2 * int(sizeof(T)) <= bytes && NN % (2 * k) == 0) k *= 2;
+    return k;
+  }
+  static constexpr int KB = NN == 128 ? rows_for(2048) : NN;
+  static constexpr size_t ZS = size_t(KB) * H;         // z stride
+  static constexpr size_t KS = ZS * NN;                // stride of a block of KB rows
+  static constexpr size_t MS = size_t(NN) * NN * H;    // moment stride
+  // z-planes of one moment side by side in the launch order of the passes
+  // that work on planes (their pieces are neighbours in HBM)
+  static constexpr int ZG = KB < NN ? 8 : 1;
+  // offset of row ky at z = 0
+  static __host__ __device__ __forceinline__ constexpr size_t row(int ky) {
+    return size_t(ky / KB) * KS + size_t(ky % KB) * H;
+  }
+  static __host__ __device__ __forceinline__ constexpr int at(int z, int ky, int kx) {
+    return int(row(ky) + size_t(z) * ZS) + kx;
+  }
+  // (z, ky) of offset p within a moment (kx = p % H)
+  static __device__ __forceinline__ int ky_of(int p) { return p / int(KS) * KB + p / H % KB; }
+  static __device__ __forceinline__ int z_of(int p) { return p / int(ZS) % NN; }
 };
 
 // LDS layout of RB packed spectral rows of H = n/2 complex values (a whole
@@ -218,6 +260,7 @@ k_fwd_plane(const T* __restrict__ src, typename cplx_of<T>::type* __restrict__ s
   using G = GridC<NN>;
   constexpr int n = NN, H = G::H;
   using Lay = PlaneLayout<NN, NN>;
+  using Spec = SpecLayout<T, NN>;
   constexpr int CNT = n * H;                     // complex values per packed plane
   constexpr int ITER = (CNT + kPBlock - 1) / kPBlock;
   if (ctl->stop) return;
@@ -250,9 +293,9 @@ k_fwd_plane(const T* __restrict__ src, typename cplx_of<T>::type* __restrict__ s
     __syncthreads();
     if (k + 1 < kFwdPlanes && plane + 1 < nplanes) gload(plane + 1);
     forward_plane_lds<V, T, NN, kPBlock>(pl, tw);
-    V* dst = spec + size_t(plane) * n * H;
+    V* dst = spec + size_t(plane / n) * Spec::MS + size_t(plane % n) * Spec::ZS;
     staged_copy<n * H, kPBlock>([&](int i) { return pl[Lay::pos(i / H, i % H)]; },
-                                [&](int i, V x) { dst[i] = x; });
+                                [&](int i, V x) { dst[Spec::row(i / H) + i % H] = x; });
     __syncthreads();
   }
 }
@@ -302,9 +345,10 @@ k_pencil(const typename cplx_of<T>::type* src, typename cplx_of<T>::type* dst,  
          const Ctl* __restrict__ ctl, long long bs = 0) {
   using V = typename cplx_of<T>::type;
   using Z = ZdShape<T, NN>;
-  constexpr int n = NN, H = NN / 2, TZ = Z::TZ, PITCH = Z::PITCH;
-  // element stride along the pencil axis in the [b][z][ky][kx] spectrum
-  constexpr size_t AX = pencil_z(MODE) ? size_t(n) * H : size_t(H);
+  constexpr int n = NN, TZ = Z::TZ, PITCH = Z::PITCH;
+  using Spec = SpecLayout<T, NN>;
+  // offset of point i along the pencil axis
+  auto axis = [](int i) { return pencil_z(MODE) ? size_t(i) * Spec::ZS : Spec::row(i); };
   src = slot_ptr(src, bs);
   dst = slot_ptr(dst, bs);
   twg = slot_ptr(twg, bs);
@@ -320,13 +364,12 @@ k_pencil(const typename cplx_of<T>::type* src, typename cplx_of<T>::type* dst,  
   const int bw = tile / Z::NTILE;
   const int kx0 = (tile - bw * Z::NTILE) * TZ;
   const int b = bw / n, w = bw - b * n;
-  const size_t base = pencil_z(MODE) ? (size_t(b) * n * n + w) * H + kx0
-                                            : (size_t(b) * n + w) * size_t(n) * H + kx0;
+  const size_t base = size_t(b) * Spec::MS + (pencil_z(MODE) ? Spec::row(w) : size_t(w) * Spec::ZS) + kx0;
   for (int i = threadIdx.x; i < n; i += kZBlock) tw[i] = twg[i];
   // element i of pencil f (bank-swizzled within the pencil)
   const SwzAt<V, n, PITCH> at{col};
   staged_copy<n * TZ, kZBlock>(
-      [&](int i) { return src[base + size_t(i / TZ) * AX + (i % TZ)]; },
+      [&](int i) { return src[base + axis(i / TZ) + (i % TZ)]; },
       [&](int i, V x) { col[(i % TZ) * PITCH + fft_swz<n>(i / TZ)] = x; });
   __syncthreads();
   if constexpr (pencil_inverse(MODE)) {
@@ -350,7 +393,7 @@ k_pencil(const typename cplx_of<T>::type* src, typename cplx_of<T>::type* dst,  
   __syncthreads();
   staged_copy<n * TZ, kZBlock>(
       [&](int i) { return col[(i % TZ) * PITCH + fft_swz<n>(i / TZ)]; },
-      [&](int i, V x) { dst[base + size_t(i / TZ) * AX + (i % TZ)] = x; });
+      [&](int i, V x) { dst[base + axis(i / TZ) + (i % TZ)] = x; });
 }
 
 // --------------------------------------------- row passes (large grids) ---
@@ -390,9 +433,11 @@ k_rows_fwd(const T* __restrict__ src, typename cplx_of<T>::type* __restrict__ sp
   __syncthreads();
   r2c_split<V, T, NN, RB, Lay, kZBlock>(pl, tw);
   __syncthreads();
-  V* dst = spec + r0 * H;
+  using Spec = SpecLayout<T, NN>;
+  const int bz = int(r0 / n), y0 = int(r0 % n);   // (b n + z), first row
+  V* dst = spec + size_t(bz / n) * Spec::MS + size_t(bz % n) * Spec::ZS;
   staged_copy<RB * H, kZBlock>([&](int i) { return pl[Lay::pos(i / H, i % H)]; },
-                               [&](int i, V x) { dst[i] = x; });
+                               [&](int i, V x) { dst[Spec::row(y0 + i / H) + i % H] = x; });
 }
 
 // --------------------------------------------------- C: moment coupling ---
@@ -514,9 +559,9 @@ k_couple(const typename cplx_of<T>::type* __restrict__ spec, typename cplx_of<T>
   ctl = slot_ptr(ctl, bs);
   if (ctl->stop) return;
   const int cls = blockIdx.x & 1;
-  const int pt = (blockIdx.x >> 1) * kCBlock + threadIdx.x;   // (z * n + ky) * H + kx
+  const int pt = (blockIdx.x >> 1) * kCBlock + threadIdx.x;
   if (pt >= n * n * H) return;
-  const T kx = kv[pt % H], ky = kv[(pt / H) % n];
+  const T kx = kv[pt % H], ky = kv[SpecLayout<T, NN>::ky_of(pt)];
   if (cls == 0) {
     couple_point<V, T, N, 0>(spec + pt, dspec + pt, MS, kx, ky, sc);
   } else if constexpr (parity_rows(N, 1) > 0) {
@@ -548,10 +593,10 @@ k_couple_rt(const typename cplx_of<T>::type* __restrict__ spec,
   constexpr int n = NN, H = NN / 2;
   constexpr size_t MS = size_t(n) * n * H;
   if (ctl->stop) return;
-  const int pt = blockIdx.x * kCBlock + threadIdx.x;   // (z * n + ky) * H + kx
+  const int pt = blockIdx.x * kCBlock + threadIdx.x;
   if (pt >= n * n * H) return;
   const int N = isqrt_c(M - 1);
-  const T kx = kv[pt % H], ky = kv[(pt / H) % n];
+  const T kx = kv[pt % H], ky = kv[SpecLayout<T, NN>::ky_of(pt)];
   for (int g = int(blockIdx.y); g <= N; g += kRtSlices)
   for (int l = g; l <= N; ++l)
   for (int sg = 0; sg < (g > 0 ? 2 : 1); ++sg) {
@@ -759,13 +804,15 @@ k_inv_plane(const typename cplx_of<T>::type* spec, const T* vin, T* u, T* dst,
   V* tw = reinterpret_cast<V*>(smem);
   V* pl = tw + n;
   // logical order z-major, moment-minor: moments of one z-plane (which
-  // share the loss maps) run back to back on one XCD
+  // share the loss maps) run back to back on one XCD, ZG planes side by side
   const int lt = xcd_tile(blockIdx.x, gridDim.x);
-  const int z = lt / M, b = lt - z * M;
-  const int plane = b * n + z;
+  using Spec = SpecLayout<T, NN>;
+  const int zg = lt / (M * Spec::ZG), rem = lt - zg * (M * Spec::ZG);
+  const int b = rem / Spec::ZG, z = zg * Spec::ZG + rem % Spec::ZG;
+  const size_t soff = size_t(b) * Spec::MS + size_t(z) * Spec::ZS;   // the plane's spectrum
   for (int i = threadIdx.x; i < n; i += kPBlock) tw[i] = twg[i];
-  const V* srcp = spec + size_t(plane) * n * H;
-  staged_copy<n * H, kPBlock>([&](int i) { return srcp[i]; },
+  const V* srcp = spec + soff;
+  staged_copy<n * H, kPBlock>([&](int i) { return srcp[Spec::row(i / H) + i % H]; },
                               [&](int i, V x) { pl[Lay::pos(i / H, i % H)] = x; });
   __syncthreads();
   fft_batch<V, n, n, +1, H, kPBlock>(tw, Lay::yat(pl));
@@ -782,9 +829,9 @@ k_inv_plane(const typename cplx_of<T>::type* spec, const T* vin, T* u, T* dst,
   if constexpr (FUSE) {
     __syncthreads();
     forward_plane_lds<V, T, NN, kPBlock>(pl, tw);
-    V* fd = fspec + size_t(plane) * n * H;
+    V* fd = fspec + soff;
     staged_copy<n * H, kPBlock>([&](int i) { return pl[Lay::pos(i / H, i % H)]; },
-                                [&](int i, V x) { fd[i] = x; });
+                                [&](int i, V x) { fd[Spec::row(i / H) + i % H] = x; });
   }
   // (block_sum2 reuses the LDS: it synchronises first)
   if ((MODE == EPI_LAST || MODE == EPI_EULER) && b == 0) block_sum2<kPBlock>(smem, acc_d, acc_o, partial + 2 * z);
@@ -792,8 +839,8 @@ k_inv_plane(const typename cplx_of<T>::type* spec, const T* vin, T* u, T* dst,
 
 // Inverse x transform + epilogue of RB rows per workgroup (grids whose
 // plane does not fit in LDS; the y transform ran before as a pencil pass).
-// Logical order (z, row block, moment) so moments sharing loss rows are
-// neighbours on one XCD. FUSE: the output rows, still in LDS, are
+// Logical order (z group, row block, moment, z in group) so moments sharing
+// loss rows are neighbours on one XCD and neighbouring z write one piece of HBM. FUSE: the output rows, still in LDS, are
 // transformed forward at once (x real-to-complex, as k_rows_fwd) and
 // written as the next stage's row spectrum to fspec (which may be the
 // spectrum just read: each workgroup owns its rows), so the next stage
@@ -813,12 +860,14 @@ k_rows_inv(const typename cplx_of<T>::type* spec, const T* vin, T* u, T* dst,
   V* tw = reinterpret_cast<V*>(smem);
   V* pl = tw + n;
   const int lt = xcd_tile(blockIdx.x, gridDim.x);
-  const int b = lt % M, zy = lt / M;
-  const int z = zy / NB, yb = zy - z * NB;
-  const int y0 = yb * RB;
+  using Spec = SpecLayout<T, NN>;
+  const int zi = lt % Spec::ZG, b = lt / Spec::ZG % M, gy = lt / (Spec::ZG * M);
+  const int z = gy / NB * Spec::ZG + zi, yb = gy % NB;
+  const int zy = z * NB + yb, y0 = yb * RB;
+  const size_t soff = size_t(b) * Spec::MS + size_t(z) * Spec::ZS;
   for (int i = threadIdx.x; i < n; i += kZBlock) tw[i] = twg[i];
-  const V* srcp = spec + ((size_t(b) * n + z) * n + y0) * H;
-  staged_copy<RB * H, kZBlock>([&](int i) { return srcp[i]; },
+  const V* srcp = spec + soff;
+  staged_copy<RB * H, kZBlock>([&](int i) { return srcp[Spec::row(y0 + i / H) + i % H]; },
                                [&](int i, V x) { pl[Lay::pos(i / H, i % H)] = x; });
   __syncthreads();
   c2r_merge<V, T, NN, RB, Lay, kZBlock>(pl, tw);
@@ -836,9 +885,9 @@ k_rows_inv(const typename cplx_of<T>::type* spec, const T* vin, T* u, T* dst,
     __syncthreads();
     r2c_split<V, T, NN, RB, Lay, kZBlock>(pl, tw);
     __syncthreads();
-    V* fd = fspec + ((size_t(b) * n + z) * n + y0) * H;
+    V* fd = fspec + soff;
     staged_copy<RB * H, kZBlock>([&](int i) { return pl[Lay::pos(i / H, i % H)]; },
-                                 [&](int i, V x) { fd[i] = x; });
+                                 [&](int i, V x) { fd[Spec::row(y0 + i / H) + i % H] = x; });
   }
   // (block_sum2 reuses the LDS: it synchronises first)
   if ((MODE == EPI_LAST || MODE == EPI_EULER) && b == 0) block_sum2<kZBlock>(smem, acc_d, acc_o, partial + 2 * zy);
@@ -1315,11 +1364,9 @@ k_expo(typename cplx_of<T>::type* __restrict__ spec, const typename cplx_of<T>::
   constexpr int M = (N + 1) * (N + 1);
   constexpr size_t MS = size_t(n) * n * H;
   constexpr int JMAX = TaylorMax<T>::value;
-  const int pt = blockIdx.x * kEBlock + threadIdx.x;   // (kz * n + ky) * H + kx
+  const int pt = blockIdx.x * kEBlock + threadIdx.x;
   if (pt >= n * n * H) return;
-  const int kxi = pt % H;
-  const int kyi = (pt / H) % n;
-  const int kzi = pt / (n * H);
+  const int kxi = pt % H, kyi = SpecLayout<T, NN>::ky_of(pt), kzi = SpecLayout<T, NN>::z_of(pt);
   const T kx = kv[kxi], ky = kv[kyi], kz = kv[kzi];
   const double kk = std::sqrt(double(kx) * kx + double(ky) * ky + double(kz) * kz);
   const double nu = p.ct * (kk + p.sigmax);
@@ -1619,7 +1666,7 @@ k_expo_frame(typename cplx_of<T>::type* __restrict__ v, const T* __restrict__ kv
   __syncthreads();
   const int pt = blockIdx.x * kEBlock + threadIdx.x;
   if (pt >= n * n * H) return;
-  const int xi = pt % H, yi = (pt / H) % n, zi = pt / (n * H);
+  const int xi = pt % H, yi = SpecLayout<T, NN>::ky_of(pt), zi = SpecLayout<T, NN>::z_of(pt);
   T cp[N + 1], sp[N + 1], ct[N + 1], st[N + 1];
   k_angles<T, N>(kv[xi], kv[yi], kv[zi], cp, sp, ct, st);
   frame_shell_of<V, T, N, BACK>(int(blockIdx.y), v + pt, MS, xs, cp, sp, ct, st, sc);
@@ -1702,9 +1749,9 @@ template <int NN> struct ExpoQuad {
   static constexpr int NCLS = OCT ? C * (C + 1) / 2 : C * C;       // (y, z) classes
   static constexpr int THREADS = NCLS * (H / TX) * G * TX;          // threads launched
   static __device__ __forceinline__ int mirror(int i) { return i == 0 ? NN / 2 : NN - i; }
-  // point index (z n + y) H + x of thread t < THREADS, or -1 (an idle lane
-  // of a diagonal class, whose swapped points are the same points)
-  static __device__ __forceinline__ int point(int t) {
+  // point (x, y, z) of thread t < THREADS; false for an idle lane of a
+  // diagonal class, whose swapped points are the same points
+  static __device__ __forceinline__ bool point(int t, int& x, int& y, int& z) {
     const int Q = t / (G * TX), l = t - Q * G * TX;
     const int sub = l / TX, xl = l - sub * TX;
     constexpr int XT = H / TX;
@@ -1712,13 +1759,12 @@ template <int NN> struct ExpoQuad {
     int yc, zc;
     if constexpr (OCT) {
       // cls -> (yc <= zc): row zc holds zc + 1 classes
-      int z = int((sqrtf(8.f * cls + 1.f) - 1.f) * 0.5f);
-      while ((z + 1) * (z + 2) / 2 <= cls) ++z;
-      while (z * (z + 1) / 2 > cls) --z;
-      zc = z;
-      yc = cls - z * (z + 1) / 2;
+      zc = int((sqrtf(8.f * cls + 1.f) - 1.f) * 0.5f);
+      while ((zc + 1) * (zc + 2) / 2 <= cls) ++zc;
+      while (zc * (zc + 1) / 2 > cls) --zc;
+      yc = cls - zc * (zc + 1) / 2;
       if (sub & 4) {
-        if (yc == zc) return -1;
+        if (yc == zc) return false;
         const int tmp = yc;
         yc = zc;
         zc = tmp;
@@ -1727,8 +1773,10 @@ template <int NN> struct ExpoQuad {
       yc = cls % C;
       zc = cls / C;
     }
-    const int y = (sub & 1) ? mirror(yc) : yc, z = (sub & 2) ? mirror(zc) : zc;
-    return (z * NN + y) * H + xt * TX + xl;
+    x = xt * TX + xl;
+    y = (sub & 1) ? mirror(yc) : yc;
+    z = (sub & 2) ? mirror(zc) : zc;
+    return true;
   }
 };
 
@@ -1737,13 +1785,13 @@ __global__ void __launch_bounds__(kEBlock)
 k_expo_blocks(typename cplx_of<T>::type* __restrict__ spec, const typename cplx_of<T>::type* __restrict__ qs,
               const typename cplx_of<T>::type* __restrict__ tab) {
   using V = typename cplx_of<T>::type;
-  constexpr int n = NN, H = NN / 2;
-  constexpr size_t MS = size_t(n) * n * H;
+  constexpr int n = NN;
+  constexpr size_t MS = SpecLayout<T, NN>::MS;
   const int t = blockIdx.x * kEBlock + threadIdx.x;
   if (t >= ExpoQuad<NN>::THREADS) return;
-  const int pt = ExpoQuad<NN>::point(t);
-  if (pt < 0) return;
-  const int xi = pt % H, yi = (pt / H) % n, zi = pt / (n * H);
+  int xi, yi, zi;
+  if (!ExpoQuad<NN>::point(t, xi, yi, zi)) return;
+  const int pt = SpecLayout<T, NN>::at(zi, yi, xi);
   auto freq = [](int i) { return i < n / 2 ? i : (i == n / 2 ? 0 : i - n); };
   const int fy = freq(yi), fz = freq(zi);
   const int f2 = xi * xi + fy * fy + fz * fz;
@@ -1757,11 +1805,12 @@ k_expo_blocks(typename cplx_of<T>::type* __restrict__ spec, const typename cplx_
 
 #include "rte_plane128.h"
 #include "rte_pencil.h"
+#include "rte_stream.h"
 
 namespace rte {
 
-// One pencil pass over all M n (n/2) / TZ tiles: the register pencils of FP32
-// 128^3 / 256^3 grids where they apply, k_pencil otherwise (ns slot rows,
+// One pencil pass over all M n (n/2) / TZ tiles: the FP32 register pencils
+// where they apply, k_pencil otherwise (ns slot rows,
 // bs slot stride for batched launches).
 template <typename T, int NN, int MODE>
 void launch_pencil(hipStream_t st, const typename cplx_of<T>::type* src, typename cplx_of<T>::type* dst,
@@ -1850,6 +1899,8 @@ hipError_t prepare_t(const StepArgs& a) {
       set(reinterpret_cast<const void*>(&p128::k_plane128<EPI_EULER, true>), p128::kLds);
     }
   }
+  if constexpr (strm::use_stream<T, NN, N>())
+    set(reinterpret_cast<const void*>(&strm::k_stream<T, NN, N>), strm::Cfg<T, NN, N>::lds());
   set(reinterpret_cast<const void*>(&k_pencil<T, NN, PENCIL_ZDERIV>), zd_lds<T, NN>());
   set(reinterpret_cast<const void*>(&k_pencil<T, NN, PENCIL_ZFWD>), zd_lds<T, NN>());
   set(reinterpret_cast<const void*>(&k_pencil<T, NN, PENCIL_ZINV>), zd_lds<T, NN>());
@@ -1907,16 +1958,22 @@ void enqueue_stage(const StepArgs& a, ProfRec* pr, double hs, double sgn, const 
     launch_fwd_plane<T, NN>(st, src, spec, tw, cctl, planes);
     rec(PROF_FWD_PLANE);
   }
-  launch_pencil<T, NN, PENCIL_ZDERIV>(st, spec, dspec, tw, kv, cctl, M, ns, bs);
-  rec(PROF_ZDERIV);
   V* coupled = dspec;   // the inverse passes read the coupled spectrum from here
-  if constexpr (N <= kDenseOrder) {
-    hipLaunchKernelGGL((k_couple<T, NN, N>), dim3(2 * cblocks, ns), cblk, 0, st, spec, dspec, kv,
-                       T(sgn * hs / n2), cctl, bs);
+  if constexpr (strm::use_stream<T, NN, N>()) {
+    using C = strm::Cfg<T, NN, N>;
+    hipLaunchKernelGGL((strm::k_stream<T, NN, N>), dim3(2 * NN * (NN / 2 / C::TZ), ns), dim3(C::BT), C::lds(), st,
+                       spec, dspec, tw, kv, T(sgn * hs / n2), cctl, bs);
   } else {
-    coupled = static_cast<V*>(a.wspec);
-    hipLaunchKernelGGL((k_couple_rt<T, NN>), dim3(cblocks, kRtSlices), cblk, 0, st, spec, dspec, coupled, kv, a.ctab,
-                       static_cast<const T*>(a.cval), M, T(sgn * hs / n2), cctl);
+    launch_pencil<T, NN, PENCIL_ZDERIV>(st, spec, dspec, tw, kv, cctl, M, ns, bs);
+    rec(PROF_ZDERIV);
+    if constexpr (N <= kDenseOrder) {
+      hipLaunchKernelGGL((k_couple<T, NN, N>), dim3(2 * cblocks, ns), cblk, 0, st, spec, dspec, kv,
+                         T(sgn * hs / n2), cctl, bs);
+    } else {
+      coupled = static_cast<V*>(a.wspec);
+      hipLaunchKernelGGL((k_couple_rt<T, NN>), dim3(cblocks, kRtSlices), cblk, 0, st, spec, dspec, coupled, kv, a.ctab,
+                         static_cast<const T*>(a.cval), M, T(sgn * hs / n2), cctl);
+    }
   }
   rec(PROF_COUPLE);
   if constexpr (split_planes<NN>()) {

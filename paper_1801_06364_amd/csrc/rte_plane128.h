@@ -34,6 +34,7 @@ namespace rte {
 namespace p128 {
 
 constexpr int n = 128, H = 64, PITCH = 65;
+using Spec = SpecLayout<float, n>;
 #ifndef RTE_P128_NT
 #define RTE_P128_NT 1
 #endif
@@ -44,6 +45,7 @@ constexpr int n = 128, H = 64, PITCH = 65;
 #define RTE_P128_BATCH 2
 #endif
 constexpr int kEpiBatch = RTE_P128_BATCH;   // epilogue quads per thread with loads in flight
+static_assert(8 % Spec::KB == 0, "rows 8 apart are whole blocks apart");
 constexpr size_t kLds = size_t(n + n * PITCH) * sizeof(float2);
 
 // Element at a 32-bit byte offset from a uniform base: the address stays a
@@ -227,7 +229,8 @@ __device__ __forceinline__ void forward_plane(float2* c0, float2* c1, float2* pl
   const unsigned lo = unsigned(ln) * 8u;
 #pragma unroll
   for (int hh = 0; hh < 2; ++hh) {
-    const int jp = wv + 8 * hh;
+    const int jp = wv + 8 * hh;   // (rows jp + 16 k: whole blocks of Spec::KB rows apart)
+    float2* fdr = fd + Spec::row(jp);
     const float2* c = pl + jp * PITCH + ln;
     float2 v[8];
 #pragma unroll
@@ -236,7 +239,7 @@ __device__ __forceinline__ void forward_plane(float2* c0, float2* c1, float2* pl
     for (int r = 1; r < 8; ++r) v[r] = cmul(v[r], twg[r * jp]);
     Bfly<float2, 8, -1>::run(v);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) st_stream(&at_b<float2>(fd, lo + unsigned((jp + 16 * k) * H * 8)), v[k]);
+    for (int k = 0; k < 8; ++k) st_stream(&at_b<float2>(fdr, lo + unsigned(Spec::row(16 * k) * 8)), v[k]);
   }
 }
 
@@ -267,7 +270,7 @@ k_fwd128(const float* __restrict__ src, float2* __restrict__ spec, const float2*
     c1[k] = cmk<float2>(x.z, x.w);
   }
   __syncthreads();
-  forward_plane(c0, c1, pl, tw, twg, spec + size_t(plane) * n * H);
+  forward_plane(c0, c1, pl, tw, twg, spec + size_t(plane / n) * Spec::MS + size_t(plane % n) * Spec::ZS);
 }
 
 template <int MODE, bool FUSE>
@@ -297,19 +300,20 @@ k_plane128(const float2* spec, const float* vin, float* u, float* dst, const flo
 #else
   const int lt = blockIdx.x;
 #endif
-  const int z = lt / M, b = lt - z * M;
-  const int plane = b * n + z;
+  const int zg = lt / (M * Spec::ZG), rem = lt - zg * (M * Spec::ZG);
+  const int b = rem / Spec::ZG, z = zg * Spec::ZG + rem % Spec::ZG;
+  const size_t soff = size_t(b) * Spec::MS + size_t(z) * Spec::ZS;   // the plane's spectrum
   const int tid = threadIdx.x, ln = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);   // wavefront index (uniform)
   if (tid < n) tw[tid] = twg[tid];
 
   // ---- inverse y, stage 1 (radix 16, from HBM): column ln, butterfly wv
   {
-    const float2* sp = spec + size_t(plane) * n * H + wv * H;
+    const float2* sp = spec + soff + Spec::row(wv);
     const unsigned lo = unsigned(ln) * 8u;
     float2 x[16];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) x[r] = ld_b<float2>(sp, lo + unsigned(8 * r * H * 8));
+    for (int r = 0; r < 16; ++r) x[r] = ld_b<float2>(sp, lo + unsigned(Spec::row(8 * r) * 8));
     Bfly<float2, 16, +1>::run(x);
     float2* d = pl + 16 * wv * PITCH + ln;
 #pragma unroll
@@ -443,7 +447,7 @@ k_plane128(const float2* spec, const float* vin, float* u, float* dst, const flo
     }
   }
 
-  if constexpr (FUSE) forward_plane(c0, c1, pl, tw, twg, fspec + size_t(plane) * n * H);
+  if constexpr (FUSE) forward_plane(c0, c1, pl, tw, twg, fspec + soff);
   // (block_sum2 reuses the LDS: it synchronises first)
   if ((MODE == EPI_LAST || MODE == EPI_EULER) && b == 0) block_sum2<512>(smem, acc_d, acc_o, partial + 2 * z);
 }

@@ -1,0 +1,446 @@
+// Streaming pass: z derivative and moment coupling in one sweep over the
+// spectrum (orders up to kDenseOrder).
+//
+// Per spectral point the streaming term of eq. (10) in the real basis is
+//   W_a = s * ( -i (kx Bx + ky By)[a,b] S_b  -  Bz[a,b] dS_b/dz ),
+// S the moments' xy spectra [b][z][ky][kx]. Every B_j moves degree l to
+// l +- 1 (eq. 6), so the rows of even degree read the odd degrees only and
+// the other way round: the operator splits into two halves that share no
+// input and no output. A workgroup owns one half Q (inputs of degree parity
+// Q, outputs of the other one), one ky and TZ kx columns at every z. Its
+// waves take the inputs one moment (tile of n x TZ points) each: load it
+// into registers, publish it in LDS, transform it along z (Stockham stages
+// exchanged through a wave-private LDS buffer), multiply by i k_z, transform
+// back and publish the derivative; then all threads add the published
+// moments of this round, at their own points, to the accumulators of every
+// output, which stay in registers for the whole sweep. Each input is read
+// from HBM once and each output written once (2F per stage, F = M n^3
+// elements, instead of 5F for a derivative pass and a coupling pass).
+//
+// Bound: HBM at 128^3 P_7 (a copy with these accesses takes 220 us), the
+// transforms and sums of eight waves per CU on top (skipping either costs
+// 25 us less); arithmetic and LDS on the smaller grids and at 256^3. Against
+// the two passes it replaces: FP32 128^3 P_7 490 -> 271 us, FP64 1003 -> 525,
+// 256^3 P_5 2345 -> 1490-1630, 64^3 P_7 55 -> 28, 64^3 P_5 32 -> 18, 96^3 P_3
+// 47 -> 39, 48^3 P_3 (eight solves) 107 -> 28, 48^3 P_4 FP64 47 -> 25. Loading
+// the next round's tiles before this round's transforms (instead of after
+// them) measured slower on every grid (128^3 P_7 375 against 365 us, 64^3 P_7
+// 37 against 28), so the loads are not waited for long.
+#pragma once
+
+namespace rte {
+namespace strm {
+
+// ---------------------------------------------------------- moment sets ---
+// degree parity of moment a, and the moments of one parity in order
+__host__ __device__ constexpr int l_parity(int a) { return isqrt_c(a) & 1; }
+__host__ __device__ constexpr int set_size(int N, int Q) {
+  int c = 0;
+  for (int l = Q; l <= N; l += 2) c += 2 * l + 1;
+  return c;
+}
+__host__ __device__ constexpr int set_at(int N, int Q, int i) {
+  for (int l = Q; l <= N; l += 2) {
+    if (i < 2 * l + 1) return l * l + i;
+    i -= 2 * l + 1;
+  }
+  return -1;
+}
+// position of moment a within its set
+__host__ __device__ constexpr int set_pos(int a) {
+  const int l = isqrt_c(a);
+  int c = a - l * l;
+  for (int k = l & 1; k < l; k += 2) c += 2 * k + 1;
+  return c;
+}
+
+// ----------------------------------------------------------------- plans ---
+// TZ columns per tile, L lanes per column with P = n / L points each, the
+// radices of the forward transform (the inverse takes them in reverse, so
+// that its first stage starts on the registers the forward ends in).
+// A row of a tile is 64 bytes (TZ = 8 FP32, 4 FP64) or 128.
+struct Plan {
+  int TZ, L, R[3], stages;
+};
+template <typename T> __host__ __device__ constexpr Plan plan_of(int n) {
+  const bool f = sizeof(T) == 4;
+  switch (n) {
+    case 16: return {8, 4, {4, 4, 1}, 2};
+    case 32: return {8, 4, {8, 4, 1}, 2};
+    case 48: return {f ? 8 : 4, 4, {12, 4, 1}, 2};
+    case 64: return {8, 8, {8, 8, 1}, 2};
+    case 96: return f ? Plan{8, 8, {12, 2, 4}, 3} : Plan{4, 8, {12, 2, 4}, 3};
+    case 128: return f ? Plan{8, 8, {16, 8, 1}, 2} : Plan{4, 16, {8, 4, 4}, 3};
+    default: return f ? Plan{8, 16, {16, 16, 1}, 2} : Plan{4, 32, {8, 8, 4}, 3};
+  }
+}
+
+#ifndef RTE_STREAM_WAVES
+#define RTE_STREAM_WAVES 0
+#endif
+
+template <typename T, int NN, int N> struct Cfg {
+  using V = typename cplx_of<T>::type;
+  using Lay = SpecLayout<T, NN>;
+  static constexpr Plan pl = plan_of<T>(NN);
+  static constexpr int n = NN, H = NN / 2, TZ = pl.TZ, L = pl.L, P = NN / L;
+  static constexpr int G = L * TZ;                       // lanes per moment tile
+  static constexpr int WPM = G > 64 ? G / 64 : 1;        // waves per moment
+  static constexpr int MPW = G < 64 ? 64 / G : 1;        // moments per wave
+  static constexpr int OUT = set_size(N, 0) > set_size(N, 1) ? set_size(N, 0) : set_size(N, 1);
+  // registers of the accumulators per thread of a workgroup of w waves
+  static constexpr int acc_regs(int w) { return OUT * (n * TZ / (64 * w)) * 2 * int(sizeof(T) / 4); }
+  // the fewest waves (a divisor of the tile's points) whose accumulators fit
+  // 168 of the 256 registers a thread has with two waves per SIMD, from eight
+  // on small grids (few workgroups: more inputs per round) and four on large
+  static constexpr int waves() {
+    if (RTE_STREAM_WAVES) return RTE_STREAM_WAVES;
+    const int full = n * TZ / 64;                        // waves at one point per thread
+    int lo = n >= 96 ? 4 : 8;
+    for (int w = 1; w <= 16; ++w)
+      if (full % w == 0 && w % WPM == 0 && (w >= lo || w == full) && acc_regs(w) <= 168) return w;
+    return full;
+  }
+  static constexpr int NW = waves(), BT = 64 * NW;
+  static constexpr int PTS = n * TZ;
+  static constexpr int VW = (PTS / BT) % 2 == 0 && sizeof(T) == 4 ? 2 : 1;   // points per 16-byte access
+  static constexpr int PPT = PTS / BT;
+  static constexpr int RK = pl.R[pl.stages - 1];         // last radix of the forward
+  static constexpr int PADROWS = n / pl.R[0] > n / RK ? n / pl.R[0] : n / RK;
+  static constexpr int DROWS = n + PADROWS;              // exchange buffer
+  static constexpr size_t lds_of(int moments) {
+    return (size_t(moments) * (size_t(n) + DROWS) * TZ + n) * sizeof(V) + size_t(n) * sizeof(T);
+  }
+  // moments per round: one tile for each wave (or part of one), no more than
+  // there are inputs, within 160 KB
+  static constexpr int moments() {
+    int m = NW * MPW / WPM;
+    while (m > MPW && (m - MPW >= OUT || lds_of(m) > 160 * 1024)) m -= MPW;
+    return m;
+  }
+  static constexpr int MPR = moments();
+  static constexpr size_t lds() { return lds_of(MPR); }
+  static_assert(PTS % BT == 0 && BT % TZ == 0 && 64 % TZ == 0, "a thread keeps its kx over its points");
+};
+
+// Configurations that run this pass: the accumulators, one column's points
+// and the addresses fit 256 registers (two waves per SIMD), a round's tiles
+// fit 160 KB of LDS, and where several waves share a tile all of them take
+// part in its barriers (N = 0 has no round). Left out: 256^3 above P_5.
+template <typename T, int NN, int N> constexpr bool use_stream() {
+  using C = Cfg<T, NN, N>;
+  return N <= kDenseOrder && C::acc_regs(C::NW) <= 168 && C::NW <= 8 && C::lds() <= 160 * 1024 &&
+         (C::WPM == 1 || C::MPR * C::WPM == C::NW || N == 0);
+}
+
+// ------------------------------------------------------------ transforms ---
+// 12-point DFT in registers: r = a + 3 b (b < 4), q = c + 4 d
+template <typename V, int DIR> __device__ __forceinline__ void dft12(V* x) {
+  using T = decltype(V::x);
+  V y[3][4];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b) y[a][b] = x[a + 3 * b];
+    Bfly<V, 4, DIR>::run(y[a]);
+  }
+#pragma unroll
+  for (int a = 1; a < 3; ++a)
+#pragma unroll
+    for (int c = 1; c < 4; ++c)   // exp(DIR 2 pi i a c / 12)
+      y[a][c] = cmul(y[a][c], cmk<V>(T(pen::cos_pi12(2 * a * c)), T(DIR) * T(pen::cos_pi12(6 - 2 * a * c))));
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    V z[3] = {y[0][c], y[1][c], y[2][c]};
+    Bfly<V, 3, DIR>::run(z);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) x[c + 4 * d] = z[d];
+  }
+}
+template <typename V, int R, int DIR> __device__ __forceinline__ void dft(V* x) {
+  if constexpr (R == 12) dft12<V, DIR>(x);
+  else Bfly<V, R, DIR>::run(x);
+}
+
+// Orders LDS accesses among the lanes that share a tile (one wave: they
+// execute in order; more: a workgroup barrier).
+template <int WPM> __device__ __forceinline__ void tile_sync() {
+  if constexpr (WPM == 1) wave_sync();
+  else __syncthreads();
+}
+
+// Stages ST.. of a transform in direction DIR (radices in reverse order for
+// the inverse), S the product of the radices done. x: inputs of stage ST,
+// [t][r] = row j + r n / R of butterfly j = l + L t; on return the outputs of
+// the last stage, [t][q] = row j + q n / R of the same butterflies.
+// The rows that a first stage writes (R j + q) are stored one row further
+// per R rows, so that the two columns groups of one LDS cycle fall in
+// different banks.
+template <class C, int DIR, int ST = 0, int S = 1>
+__device__ __forceinline__ void stages(typename C::V* x, typename C::V* buf, int l, int kx, const typename C::V* tw) {
+  using V = typename C::V;
+  constexpr int n = C::n, L = C::L, P = C::P, NS = C::pl.stages;
+  constexpr int R = DIR < 0 ? C::pl.R[ST] : C::pl.R[NS - 1 - ST];
+  constexpr int NB = P / R, SPAN = n / (S * R);
+  static_assert(P % R == 0, "whole butterflies per lane");
+#pragma unroll
+  for (int t = 0; t < NB; ++t) {
+    if constexpr (S > 1) {
+      const int k = (l + L * t) % S;
+#pragma unroll
+      for (int r = 1; r < R; ++r) {
+        V w = tw[r * k * SPAN];
+        if constexpr (DIR > 0) w.y = -w.y;
+        x[t * R + r] = cmul(x[t * R + r], w);
+      }
+    }
+    dft<V, R, DIR>(x + t * R);
+  }
+  if constexpr (ST + 1 < NS) {
+    constexpr int R2 = DIR < 0 ? C::pl.R[ST + 1] : C::pl.R[NS - 2 - ST];
+    constexpr int PADR = S == 1 ? R : 0;
+    static_assert(PADR == 0 || (n / R2) % (PADR ? PADR : 1) == 0, "padding splits over the rows read");
+#pragma unroll
+    for (int t = 0; t < NB; ++t) {
+      const int j = l + L * t;
+      const int o = S == 1 ? j * (R + 1) : (j / S) * S * R + j % S;
+#pragma unroll
+      for (int q = 0; q < R; ++q) buf[(o + q * S) * C::TZ + kx] = x[t * R + q];
+    }
+    tile_sync<C::WPM>();
+#pragma unroll
+    for (int t = 0; t < P / R2; ++t) {
+      const int j = l + L * t;
+      const int o = PADR ? j + j / (PADR ? PADR : 1) : j;
+      constexpr int st = n / R2 + (PADR ? n / R2 / (PADR ? PADR : 1) : 0);
+#pragma unroll
+      for (int r = 0; r < R2; ++r) x[t * R2 + r] = buf[(o + r * st) * C::TZ + kx];
+    }
+    tile_sync<C::WPM>();
+    stages<C, DIR, ST + 1, S * R>(x, buf, l, kx, tw);
+  }
+}
+
+// -------------------------------------------------------------- coupling ---
+// acc[pos(a)] += B[a, b] (X | Y | Z)_b for every output a that reads input
+// b = set_at(N, Q, I): X = s kx (Im S, -Re S), Y the same with ky, Z = -s D.
+template <class C, typename T, int N, int B, int S>
+struct Scatter {
+  static __device__ __forceinline__ void run(typename C::V (*acc)[C::VW], const typename C::V* X,
+                                             const typename C::V* Y, const typename C::V* Z) {
+    constexpr int l = isqrt_c(B);
+    constexpr SlotList sl = slots_of(N, l, B - l * l - l);
+    if constexpr (S < sl.count) {
+      constexpr int a = sl.b[S];
+      constexpr double c0 = ct::real_coef(N, 0, a, B), c1 = ct::real_coef(N, 1, a, B), c2 = ct::real_coef(N, 2, a, B);
+      constexpr int p = set_pos(a);
+#pragma unroll
+      for (int v = 0; v < C::VW; ++v) {
+        if constexpr (c0 != 0.0) {
+          acc[p][v].x += T(c0) * X[v].x;
+          acc[p][v].y += T(c0) * X[v].y;
+        }
+        if constexpr (c1 != 0.0) {
+          acc[p][v].x += T(c1) * Y[v].x;
+          acc[p][v].y += T(c1) * Y[v].y;
+        }
+        if constexpr (c2 != 0.0) {
+          acc[p][v].x += T(c2) * Z[v].x;
+          acc[p][v].y += T(c2) * Z[v].y;
+        }
+      }
+      Scatter<C, T, N, B, S + 1>::run(acc, X, Y, Z);
+    }
+  }
+};
+
+// The published moments I.. of round RD, at item `e` (VW points) of a thread.
+template <class C, typename T, int N, int Q, int RD, int I>
+__device__ __forceinline__ void add_round(typename C::V (*acc)[C::VW], const typename C::V* pub, int e,
+                                          const T* skx, T sky) {
+  using V = typename C::V;
+  constexpr int i = RD * C::MPR + I;
+  if constexpr (I < C::MPR && i < set_size(N, Q)) {
+    constexpr int b = set_at(N, Q, i);
+    const V* s = pub + I * (C::n + C::DROWS) * C::TZ + e;
+    const V* d = s + C::n * C::TZ;
+    V X[C::VW], Y[C::VW], Z[C::VW];
+    if constexpr (C::VW == 2) {
+      const float4 sv = *reinterpret_cast<const float4*>(s), dv = *reinterpret_cast<const float4*>(d);
+      X[0] = cmk<V>(sv.y, -sv.x);
+      X[1] = cmk<V>(sv.w, -sv.z);
+      Z[0] = cmk<V>(dv.x, dv.y);
+      Z[1] = cmk<V>(dv.z, dv.w);
+    } else {
+      const V sv = *s;
+      X[0] = cmk<V>(sv.y, -sv.x);
+      Z[0] = *d;
+    }
+#pragma unroll
+    for (int v = 0; v < C::VW; ++v) {
+      Y[v] = cscale(X[v], sky);
+      X[v] = cscale(X[v], skx[v]);
+    }
+    Scatter<C, T, N, b, 0>::run(acc, X, Y, Z);
+    // (else the LDS reads of the whole round are hoisted above the sums)
+    if constexpr (I % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+    add_round<C, T, N, Q, RD, I + 1>(acc, pub, e, skx, sky);
+  }
+}
+// Workgroup barrier that orders LDS only: loads of the next round stay in
+// flight across it.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Loads the tile of input g of round RD (rows l + L t + n / R0 r, column kx).
+template <class C, int N, int Q, int RD>
+__device__ __forceinline__ void load_tile(typename C::V* x, const typename C::V* __restrict__ src, int g, int gl) {
+  constexpr int IN = set_size(N, Q), n = C::n, R0 = C::pl.R[0];
+  constexpr size_t AX = C::Lay::ZS, MS = C::Lay::MS;
+  const int i = RD * C::MPR + g;
+  if (g < C::MPR && i < IN) {
+    int b = i, l = Q;   // moment i of the set: degrees Q, Q + 2, ...
+    while (b >= 2 * l + 1) {
+      b -= 2 * l + 1;
+      l += 2;
+    }
+    const typename C::V* s = src + size_t(l * l + b) * MS;
+    asm volatile("" : "+v"(gl));   // (see `rounds`)
+    const unsigned lo = unsigned(gl / C::TZ) * unsigned(AX) + gl % C::TZ;
+#pragma unroll
+    for (int t = 0; t < C::P / R0; ++t)
+#pragma unroll
+      for (int r = 0; r < R0; ++r) x[t * R0 + r] = (s + (size_t(C::L) * t + size_t(n / R0) * r) * AX)[lo];
+  }
+}
+
+template <class C, typename T, int N, int Q, int RD>
+__device__ __forceinline__ void rounds(typename C::V (*acc)[set_size(N, 1 - Q)][C::VW], typename C::V* x,
+                                       const typename C::V* __restrict__ src, typename C::V* pub,
+                                       const typename C::V* tw, const T* kz, const T* skx, T sky, int g, int gl) {
+  using V = typename C::V;
+  constexpr int IN = set_size(N, Q);
+  if constexpr (RD * C::MPR < IN) {
+    constexpr int n = C::n, TZ = C::TZ, L = C::L, P = C::P, R0 = C::pl.R[0], RK = C::RK;
+    if ((g < C::MPR && RD * C::MPR + g < IN) || C::WPM > 1) {
+      // opaque copy: the index arithmetic of the stages is redone in every
+      // round instead of being held in registers across the rounds
+      int o = gl;
+      asm volatile("" : "+v"(o));
+      const int kx = o % TZ, l = (o / TZ) % L;
+      V* own = pub + g * (n + C::DROWS) * TZ;
+      V* ex = own + n * TZ;
+#pragma unroll
+      for (int t = 0; t < P / R0; ++t)
+#pragma unroll
+        for (int r = 0; r < R0; ++r) own[(l + L * t + n / R0 * r) * TZ + kx] = x[t * R0 + r];
+      stages<C, -1>(x, ex, l, kx, tw);
+#pragma unroll
+      for (int t = 0; t < P / RK; ++t)
+#pragma unroll
+        for (int r = 0; r < RK; ++r) {
+          const T k = kz[l + L * t + n / RK * r];
+          x[t * RK + r] = cmk<V>(-k * x[t * RK + r].y, k * x[t * RK + r].x);
+        }
+      stages<C, +1>(x, ex, l, kx, tw);
+#pragma unroll
+      for (int t = 0; t < P / R0; ++t)
+#pragma unroll
+        for (int r = 0; r < R0; ++r) ex[(l + L * t + n / R0 * r) * TZ + kx] = x[t * R0 + r];
+    }
+    load_tile<C, N, Q, RD + 1>(x, src, g, gl);
+    lds_barrier();
+    int e = int(threadIdx.x) * C::VW;
+    asm volatile("" : "+v"(e));
+#pragma unroll
+    for (int k = 0; k < C::PPT / C::VW; ++k) add_round<C, T, N, Q, RD, 0>(acc[k], pub, e + k * C::BT * C::VW, skx, sky);
+    // the sums are formed here (the compiler would sink them to the stores
+    // and hold the published values of every round instead)
+#pragma unroll
+    for (int k = 0; k < C::PPT / C::VW; ++k)
+#pragma unroll
+      for (int a = 0; a < set_size(N, 1 - Q); ++a)
+#pragma unroll
+        for (int v = 0; v < C::VW; ++v) asm volatile("" : "+v"(acc[k][a][v].x), "+v"(acc[k][a][v].y));
+    lds_barrier();
+    rounds<C, T, N, Q, RD + 1>(acc, x, src, pub, tw, kz, skx, sky, g, gl);
+  }
+}
+
+template <class C, typename T, int N, int Q>
+__device__ __forceinline__ void sweep(const typename C::V* __restrict__ src, typename C::V* __restrict__ dst,
+                                      typename C::V* pub, const typename C::V* tw, const T* kz, const T* skx, T sky) {
+  using V = typename C::V;
+  constexpr int OUTQ = set_size(N, 1 - Q);
+  if constexpr (OUTQ > 0) {
+    constexpr int TZ = C::TZ, NI = C::PPT / C::VW;
+    constexpr size_t AX = C::Lay::ZS, MS = C::Lay::MS;
+    const int tid = threadIdx.x;
+    const int g = C::MPW == 1 ? __builtin_amdgcn_readfirstlane(tid / C::G) : tid / C::G;   // moment slot of this lane
+    V acc[NI][OUTQ][C::VW];
+#pragma unroll
+    for (int k = 0; k < NI; ++k)
+#pragma unroll
+      for (int a = 0; a < OUTQ; ++a)
+#pragma unroll
+        for (int v = 0; v < C::VW; ++v) acc[k][a][v] = cmk<V>(T(0), T(0));
+    V x[C::P];
+    load_tile<C, N, Q, 0>(x, src, g, tid % C::G);
+    rounds<C, T, N, Q, 0>(acc, x, src, pub, tw, kz, skx, sky, g, tid % C::G);
+#pragma unroll
+    for (int k = 0; k < NI; ++k) {
+      // (k moves a whole number of rows: uniform base, one lane offset)
+      const int e = tid * C::VW;
+      const unsigned lo = unsigned(e / TZ) * unsigned(AX) + e % TZ;
+#pragma unroll
+      for (int a = 0; a < OUTQ; ++a) {
+        V* o = dst + (size_t(set_at(N, 1 - Q, a)) * MS + size_t(k * C::BT * C::VW / TZ) * AX) + lo;
+        if constexpr (C::VW == 2)
+          *reinterpret_cast<float4*>(o) = make_float4(acc[k][a][0].x, acc[k][a][0].y, acc[k][a][1].x, acc[k][a][1].y);
+        else *o = acc[k][a][0];
+      }
+    }
+  }
+}
+
+// Grid: (ky, kx tile, Q), neighbouring tiles on one XCD. sc: the factor s.
+template <typename T, int NN, int N>
+__global__ void __launch_bounds__((Cfg<T, NN, N>::BT), 2)
+k_stream(const typename cplx_of<T>::type* __restrict__ spec, typename cplx_of<T>::type* __restrict__ wspec,
+         const typename cplx_of<T>::type* __restrict__ twg, const T* __restrict__ kv, T sc,
+         const Ctl* __restrict__ ctl, long long bs) {
+  using C = Cfg<T, NN, N>;
+  using V = typename C::V;
+  constexpr int n = NN, TZ = C::TZ, NT = C::H / TZ;
+  spec = slot_ptr(spec, bs);
+  wspec = slot_ptr(wspec, bs);
+  twg = slot_ptr(twg, bs);
+  kv = slot_ptr(kv, bs);
+  ctl = slot_ptr(ctl, bs);
+  if (ctl->stop) return;
+  extern __shared__ __align__(16) unsigned char smem[];
+  V* pub = reinterpret_cast<V*>(smem);
+  V* tw = pub + C::MPR * (n + C::DROWS) * TZ;
+  T* kz = reinterpret_cast<T*>(tw + n);
+  const int lt = xcd_tile(blockIdx.x, gridDim.x);
+  const int Q = lt & 1, tile = lt >> 1;
+  const int ky = tile / NT, kx0 = (tile - ky * NT) * TZ;
+  for (int i = threadIdx.x; i < n; i += C::BT) {
+    tw[i] = twg[i];
+    kz[i] = -sc * (kv[i] / T(n));
+  }
+  T skx[C::VW];
+#pragma unroll
+  for (int v = 0; v < C::VW; ++v) skx[v] = sc * kv[kx0 + (int(threadIdx.x) * C::VW) % TZ + v];
+  const T sky = sc * kv[ky];
+  const size_t off = C::Lay::row(ky) + kx0;
+  lds_barrier();
+  if (Q == 0) sweep<C, T, N, 0>(spec + off, wspec + off, pub, tw, kz, skx, sky);
+  else sweep<C, T, N, 1>(spec + off, wspec + off, pub, tw, kz, skx, sky);
+}
+
+}  // namespace strm
+}  // namespace rte

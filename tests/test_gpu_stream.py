@@ -1,0 +1,121 @@
+"""The streaming pass (z derivative and moment coupling in one sweep, halves
+by degree parity) against the oracle, and in FP64 against the same operator in
+long double (the oracle's own rounding of this difference is 1e-14): one explicit Euler step of a state with
+every moment random, in a medium without loss, so that the difference of the
+two states is the streaming term alone.
+
+Every grid family (one to four tiles per wavefront, two and three transform
+stages, tiles shared by two wavefronts at 256) and the orders where the
+split can go wrong: one empty half (P_0), halves of 1 and 3 moments (P_1),
+even and odd N, a round that is not full, and the largest halves that run
+(36 moments at P_7).
+
+Tolerances, relative L2 of the streaming term: a transform pair of
+log2(n^3) stages each way and at most 10 products per row accumulate rounding
+like sqrt(2 * 3 * log2(n) + 10) units in the last place, below 8 for n = 256;
+ten times that is 80 * 2^-24 = 5e-6 in FP32 and 80 * 2^-53 = 1e-14 in FP64.
+The step is read back as u + dt c S u with |dt c S u| >= 0.1 |u|, which adds
+one rounding of u: ten more units.
+"""
+import numpy as np
+import pytest
+import scipy.fft as sfft
+
+from oracle import pn
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"f32": 6e-6, "f64": 1.2e-14}
+
+CASES = [
+    # (n, orders)
+    (16, (0, 1, 2, 3, 4, 5, 6, 7)),
+    (32, (1, 4, 7)),
+    (48, (1, 3, 6, 7)),
+    (64, (2, 5, 7)),
+    (96, (1, 3, 6)),
+    (128, (1, 2, 3)),
+]
+
+
+def _long_double_term(n, N, dx, c, dt, psi):
+    """-dt c (B . grad) psi in long double, with the coefficients of eq. (6)."""
+    L = np.longdouble
+    f = np.fft.fftfreq(n) * n
+    f[n // 2] = 0.0
+    k = (2 * np.arccos(L(-1)) / (n * L(dx))) * f.astype(L)
+    kx = k[: n // 2 + 1].copy()
+    kx[-1] = 0.0
+    kk = (kx[None, None, :], k[None, :, None], k[:, None, None])
+    S = sfft.rfftn(psi.astype(L), axes=(1, 2, 3), workers=16)
+    W = np.zeros_like(S)
+    for j, B in enumerate(pn.real_coupling(N)):
+        for a, b in zip(*np.nonzero(np.abs(B) > 1e-13)):
+            W[a] += L(B[a, b]) * kk[j] * S[b]
+    return (L(dt) * L(c) * sfft.irfftn(-1j * W, s=(n, n, n), axes=(1, 2, 3), workers=16)).astype(np.float64)
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("n,N", [(n, N) for n, orders in CASES for N in orders])
+def test_streaming_term_of_random_state(n, N, prec):
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1801_06364_amd.rte import Solver
+    print(f"\n[stream] n={n} N={N} {prec}", flush=True)
+    M, dx, c, dt = (N + 1) ** 2, 0.25, 0.3, 0.2
+    rng = np.random.default_rng(1000 * n + N)
+    psi = rng.standard_normal((M, n, n, n))
+    if prec == "f32":
+        psi = psi.astype(np.float32).astype(np.float64)
+    zero = np.zeros((n, n, n))
+    s = Solver(n, N, dx, c, dt, zero, zero, zero, psi0=psi, precision=prec, scheme="euler",
+               stream=torch.cuda.Stream())
+    s.step(1)
+    got = s.get_state() - psi
+    s.close()
+    if N == 0:   # no degree to couple to: the streaming term is zero
+        assert np.abs(got).max() <= TOL[prec] * np.abs(psi).max()
+        return
+    if prec == "f64":
+        ref = _long_double_term(n, N, dx, c, dt, psi)
+    else:
+        ref = pn.solve(n, N, dx, c, dt, zero, zero, zero, psi, None, 0, 0.01, 1.0, 1, scheme="euler")["state"] - psi
+    assert np.linalg.norm(ref) >= 0.1 * np.linalg.norm(psi)
+    assert np.linalg.norm(got - ref) <= TOL[prec] * np.linalg.norm(ref)
+    for a in range(M):
+        assert np.linalg.norm(got[a] - ref[a]) <= 2 * TOL[prec] * np.linalg.norm(ref) / np.sqrt(M), a
+
+
+def test_streaming_term_256_p5_against_torch():
+    """256^3 P_5 (a tile shared by two wavefronts, 21-moment halves): the same
+    against a plain torch FP64 evaluation on the device."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1801_06364_amd.rte import Solver
+    n, N, dx, c, dt = 256, 5, 0.25, 0.3, 0.2
+    M = (N + 1) ** 2
+    print("\n[stream] n=256 N=5 f32 against torch", flush=True)
+    zero = np.zeros((n, n, n))
+    s = Solver(n, N, dx, c, dt, zero, zero, zero, precision="f32", scheme="euler", stream=torch.cuda.Stream())
+    g = torch.Generator(device="cuda").manual_seed(5)
+    psi = torch.randn(M, n, n, n, generator=g, device="cuda", dtype=torch.float32).double()
+    s.set_state_device(psi.view(-1))
+    s.step(1)
+    torch.cuda.synchronize()
+    k = torch.fft.fftfreq(n, d=dx / (2 * np.pi), dtype=torch.float64, device="cuda")
+    k[n // 2] = 0.0
+    kx = k[: n // 2 + 1].clone()
+    kx[-1] = 0.0
+    kk = (kx[None, None, :], k[None, :, None], k[:, None, None])
+    S = torch.fft.rfftn(psi, dim=(1, 2, 3))
+    got = torch.from_numpy(s.get_state()[:9]).cuda() - psi[:9]
+    s.close()
+    for a in range(9):   # rows of both halves, all three axes
+        w = torch.zeros_like(S[0])
+        for j, B in enumerate(pn.real_coupling(N)):
+            for b in np.flatnonzero(B[a]):
+                w += float(B[a, b]) * kk[j] * S[b]
+        ref = dt * c * torch.fft.irfftn(-1j * w, s=(n, n, n))
+        assert float((got[a] - ref).norm()) <= 2 * TOL["f32"] * float(ref.norm()), a
