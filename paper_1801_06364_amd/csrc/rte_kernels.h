@@ -6,7 +6,7 @@
 // spectrally (eqs. 7-10; sign form of eqs. 1 and 6). Since the B_j are
 // constant matrices, the z derivative can be taken per moment before the
 // moments are mixed, which keeps every sweep over HBM coalesced:
-//   F  k_fwd_plane  per (moment, z-plane): x real-to-complex FFT and y FFT of
+//   F  k_fwd        per (moment, z-plane): x real-to-complex FFT and y FFT of
 //                   the plane in LDS -> xy spectrum S [b][z][ky][kx];
 //   W  k_stream     per (ky, a few kx columns, degree parity): z derivative
 //                   D = d/dz S (xy spectral, z physical) of every moment and
@@ -18,7 +18,7 @@
 //   C  k_couple     per spectral point, all moments in registers: W, written
 //                   over D (k_couple_rt for P_21: a run-time slot table, W to
 //                   a separate buffer);
-//   P  k_inv_plane  per (moment, z-plane): inverse y FFT, complex-to-real x
+//   P  k_plane      per (moment, z-plane): inverse y FFT, complex-to-real x
 //                   FFT and the fused pointwise epilogue (loss, in-scatter,
 //                   boundary layer, source, RK combine; after the last stage
 //                   also the integrated fluence and fluence-change partials);
@@ -33,7 +33,7 @@
 // L2. Tiles that share data (neighbouring kx tiles in D, the moments of one
 // z-plane that read the same loss map in P) are remapped so that
 // consecutive logical tiles run on the same XCD. Planes and pencils sit in
-// LDS in bank-swizzled layouts (PlaneLayout, fft_swz) so that the Stockham
+// LDS in bank-swizzled layouts (RowsLayout, fft_swz) so that the Stockham
 // stages run without bank conflicts.
 #pragma once
 
@@ -45,9 +45,6 @@
 #include "rte_fft.h"
 #include "rte_internal.h"
 
-#ifndef RTE_PBLOCK
-#define RTE_PBLOCK 512
-#endif
 #ifndef RTE_ZBLOCK
 #define RTE_ZBLOCK 256
 #endif
@@ -58,13 +55,8 @@
 namespace rte {
 
 constexpr int kBlock = 256;        // end-of-step kernel
-constexpr int kPBlock = RTE_PBLOCK;  // plane passes
 constexpr int kZBlock = RTE_ZBLOCK;  // z-derivative pass
 constexpr int kCBlock = RTE_CBLOCK;  // coupling pass
-#ifndef RTE_FPPW
-#define RTE_FPPW 1
-#endif
-constexpr int kFwdPlanes = RTE_FPPW;  // planes per forward-plane workgroup
 constexpr int kXcds = 8;
 
 // Physical block id -> logical tile: XCD x (= bid % 8) receives a contiguous
@@ -85,13 +77,6 @@ __device__ __forceinline__ P* slot_ptr(P* p, long long bs) {
   return reinterpret_cast<P*>(reinterpret_cast<B*>(p) + (long long)blockIdx.y * bs);
 }
 
-template <int NN> struct GridC {
-  static constexpr int n = NN;
-  static constexpr int H = NN / 2;
-  static constexpr int E = elems_per_lane(NN);
-  static_assert(elems_per_lane(NN / 2) == elems_per_lane(NN), "row/column lane shape");
-};
-
 // Layout of the xy spectra in HBM: [b][ky / KB][z][ky % KB][kx], kx < n/2.
 // KB = n (the rows of a z-plane together) leaves a z pencil of a few kx
 // columns in 64-byte pieces a whole plane apart: a copy kernel with the
@@ -99,8 +84,9 @@ template <int NN> struct GridC {
 // P_7 FP32. With the rows of a few ky values of every z together (pieces of
 // 2 KB: KB = 4 FP32, 2 FP64) it reaches 4.8 TB/s (1 KB 5.1, 4 KB 3.5), and the
 // plane passes, which then move 2 KB pieces, keep their time if ZG = 8
-// z-planes of a moment run side by side (k_plane128: 575 us against 648 with
-// ZG = 1, 591 with 2, 572 with 16). The streaming pass itself: 333 -> 271 us
+// z-planes of a moment run side by side (measured on the 128^3 P_7 FP32
+// pass of the middle stages: 575 us against 648 with ZG = 1, 591 with 2, 572
+// with 16). The streaming pass itself: 333 -> 271 us
 // FP32, 647 -> 525 FP64. Smaller grids sit in the caches, and at 256^3 the
 // two y passes and the row pass lose what the streaming pass gains (per
 // stage 6.14 ms either way): KB = n there.
@@ -130,69 +116,24 @@ template <typename T, int NN> struct SpecLayout {
   static __device__ __forceinline__ int z_of(int p) { return p / int(ZS) % NN; }
 };
 
-// LDS layout of RB packed spectral rows of H = n/2 complex values (a whole
-// plane when RB = n). Default: row pitch H + 1 (odd, so the strided column
-// accesses of the y transform spread over the banks). The 128-point plane
-// is transformed along both axes by radix-8 Stockham stages whose stride-8
-// writes alias on that layout; it uses pitch H + 8 and stores column c of
-// row r at c ^ ((c >> 3) & 7) ^ x(r >> 1), where the row term
-// x(q) = ((q ^ (q >> 3)) & 7) | ((q & 4) << 1) spreads the 16 rows that one
-// LDS cycle touches in every y stage over distinct banks and keeps the two
-// rows one cycle touches in the x stages on complementary halves. Row blocks
-// of the large-grid kernels (RB < n, x transforms only) use the in-row
-// swizzle of contiguous FFTs.
-template <int NN, int RB> struct PlaneLayout {
+// LDS layout of RB packed spectral rows of H = n/2 complex values (the row
+// blocks of the large-grid kernels, x transforms only): row pitch H + 1, the
+// in-row swizzle of contiguous FFTs where H is a power of two.
+template <int NN, int RB> struct RowsLayout {
   static constexpr int H = NN / 2;
-  static constexpr bool SWZ = (NN == 128 && RB == NN);
-  static constexpr bool ROWSWZ = (RB < NN && H >= 64 && (H & (H - 1)) == 0);
-  static constexpr int PITCH = SWZ ? H + 8 : H + 1;
+  static constexpr bool SWZ = H >= 64 && (H & (H - 1)) == 0;
+  static constexpr int PITCH = H + 1;
   static constexpr int SIZE = RB * PITCH;
-  // column swizzle and row-pair term of the 128-point plane (both linear
-  // over GF(2), so they split over disjoint index parts)
-  static __device__ __forceinline__ int cs(int c) { return c ^ ((c >> 3) & 7); }
-  static __device__ __forceinline__ int rx(int r) {
-    const int q = r >> 1;
-    return ((q ^ (q >> 3)) & 7) | ((q << 1) & 8);
-  }
   static __device__ __forceinline__ int pos(int row, int col) {
-    if constexpr (SWZ) return row * PITCH + (cs(col) ^ rx(row));
-    else if constexpr (ROWSWZ) return row * PITCH + fft_swz<H>(col);
-    else return row * PITCH + col;
+    return row * PITCH + (SWZ ? fft_swz<H>(col) : col);
   }
-  // x transforms of the 128-point plane: FFT f = row f, element i = column i
-  template <typename V> struct XSwz {
-    static constexpr bool kXor = true;
-    V* p0;
-    struct Lane { V* q; int x; };
-    __device__ __forceinline__ Lane lane(int f, int a) const { return {p0 + f * PITCH, cs(a) ^ rx(f)}; }
-    __device__ __forceinline__ V* elem(Lane l, int b) const { return l.q + (l.x ^ cs(b)); }
-  };
-  // y transforms of the 128-point plane: FFT f = column f, element i = row i
-  template <typename V> struct YSwz {
-    static constexpr bool kXor = true;
-    V* p0;
-    struct Lane { V* q; int x; };
-    __device__ __forceinline__ Lane lane(int f, int a) const { return {p0 + a * PITCH, cs(f) ^ rx(a)}; }
-    __device__ __forceinline__ V* elem(Lane l, int b) const { return l.q + b * PITCH + (l.x ^ rx(b)); }
-  };
-  // accessors of the row (x) and column (y) transforms
+  // accessor of the row (x) transforms
   template <typename V> static __device__ __forceinline__ auto xat(V* pl) {
-    if constexpr (SWZ) return XSwz<V>{pl};
-    else if constexpr (ROWSWZ) return SwzAt<V, H, PITCH>{pl};
+    if constexpr (SWZ) return SwzAt<V, H, PITCH>{pl};
     else return AffineAt<V, PITCH, 1>{pl};
-  }
-  template <typename V> static __device__ __forceinline__ auto yat(V* pl) {
-    if constexpr (SWZ) return YSwz<V>{pl};
-    else return AffineAt<V, 1, PITCH>{pl};
   }
 };
 
-template <typename T, int NN>
-constexpr size_t plane_lds() {
-  // twiddles (n) + the plane
-  const size_t b = (size_t(PlaneLayout<NN, NN>::SIZE) + NN) * 2 * sizeof(T);
-  return b < 2 * kPBlock * 8 ? 2 * kPBlock * 8 : b;
-}
 // ---------------------------------------------------------- F: forward ---
 
 // Real-to-complex split of RB rows of packed x transforms Z (layout Lay):
@@ -234,72 +175,6 @@ __device__ __forceinline__ void r2c_split(V* pl, const V* tw) {
 // later operator treats them alike and they travel packed as one complex
 // column kx = 0 holding (X_0, X_{n/2}). The half spectrum is therefore
 // exactly n/2 columns wide: [b][z][ky][kx], kx in [0, n/2).
-// Forward transform of one real plane held in LDS as n rows of H packed
-// complex values (PlaneLayout): x real-to-complex FFT with the
-// kx = 0 / n/2 packing, then y FFT of the H columns. Callers synchronise
-// before (plane written) and read the spectrum after (ends synchronised).
-template <typename V, typename T, int NN, int BLOCK>
-__device__ __forceinline__ void forward_plane_lds(V* pl, const V* tw) {
-  constexpr int n = NN, H = NN / 2;
-  using Lay = PlaneLayout<NN, NN>;
-  // x: n packed rows of length H (twiddle table of length n, stride 2)
-  fft_batch<V, H, 2 * H, -1, n, BLOCK>(tw, Lay::xat(pl));
-  __syncthreads();
-  r2c_split<V, T, NN, n, Lay, BLOCK>(pl, tw);
-  __syncthreads();
-  // y: H columns of length n
-  fft_batch<V, n, n, -1, H, BLOCK>(tw, Lay::yat(pl));
-  __syncthreads();
-}
-
-template <typename T, int NN>
-__global__ void __launch_bounds__(kPBlock)
-k_fwd_plane(const T* __restrict__ src, typename cplx_of<T>::type* __restrict__ spec,
-            const typename cplx_of<T>::type* __restrict__ twg, const Ctl* __restrict__ ctl, int nplanes) {
-  using V = typename cplx_of<T>::type;
-  using G = GridC<NN>;
-  constexpr int n = NN, H = G::H;
-  using Lay = PlaneLayout<NN, NN>;
-  using Spec = SpecLayout<T, NN>;
-  constexpr int CNT = n * H;                     // complex values per packed plane
-  constexpr int ITER = (CNT + kPBlock - 1) / kPBlock;
-  if (ctl->stop) return;
-  extern __shared__ __align__(16) unsigned char smem[];
-  V* tw = reinterpret_cast<V*>(smem);
-  V* pl = tw + n;
-  for (int i = threadIdx.x; i < n; i += kPBlock) tw[i] = twg[i];
-  // kFwdPlanes consecutive planes per workgroup; the next plane's loads are
-  // issued into registers before the current plane's FFTs, so HBM traffic
-  // overlaps the LDS work
-  const int p0 = blockIdx.x * kFwdPlanes;
-  V pre[ITER];
-  auto gload = [&](int plane) {
-    const V* s = reinterpret_cast<const V*>(src + size_t(plane) * n * n);
-#pragma unroll
-    for (int it = 0; it < ITER; ++it) {
-      const int i = int(threadIdx.x) + it * kPBlock;
-      if (CNT % kPBlock == 0 || i < CNT) pre[it] = s[i];
-    }
-  };
-  gload(p0);
-  for (int k = 0; k < kFwdPlanes; ++k) {
-    const int plane = p0 + k;                    // b * n + z
-    if (plane >= nplanes) break;
-#pragma unroll
-    for (int it = 0; it < ITER; ++it) {
-      const int i = int(threadIdx.x) + it * kPBlock;
-      if (CNT % kPBlock == 0 || i < CNT) pl[Lay::pos(i / H, i % H)] = pre[it];
-    }
-    __syncthreads();
-    if (k + 1 < kFwdPlanes && plane + 1 < nplanes) gload(plane + 1);
-    forward_plane_lds<V, T, NN, kPBlock>(pl, tw);
-    V* dst = spec + size_t(plane / n) * Spec::MS + size_t(plane % n) * Spec::ZS;
-    staged_copy<n * H, kPBlock>([&](int i) { return pl[Lay::pos(i / H, i % H)]; },
-                                [&](int i, V x) { dst[Spec::row(i / H) + i % H] = x; });
-    __syncthreads();
-  }
-}
-
 // ------------------------------------------------ pencil passes (D, Y) ---
 
 // Pencils of 16 (or fewer) kx columns of the xy spectrum along one axis, all
@@ -408,8 +283,8 @@ template <int NN> struct RowShape {
 
 template <typename T, int NN>
 constexpr size_t rows_lds() {
-  const size_t b = (size_t(PlaneLayout<NN, RowShape<NN>::RB>::SIZE) + NN) * 2 * sizeof(T);
-  return b < 2 * kPBlock * 8 ? 2 * kPBlock * 8 : b;
+  const size_t b = (size_t(RowsLayout<NN, RowShape<NN>::RB>::SIZE) + NN) * 2 * sizeof(T);
+  return b < 2 * kZBlock * 8 ? 2 * kZBlock * 8 : b;
 }
 
 template <typename T, int NN>
@@ -418,7 +293,7 @@ k_rows_fwd(const T* __restrict__ src, typename cplx_of<T>::type* __restrict__ sp
            const typename cplx_of<T>::type* __restrict__ twg, const Ctl* __restrict__ ctl) {
   using V = typename cplx_of<T>::type;
   constexpr int n = NN, H = NN / 2, RB = RowShape<NN>::RB;
-  using Lay = PlaneLayout<NN, RB>;
+  using Lay = RowsLayout<NN, RB>;
   if (ctl->stop) return;
   extern __shared__ __align__(16) unsigned char smem[];
   V* tw = reinterpret_cast<V*>(smem);
@@ -665,11 +540,7 @@ __device__ __forceinline__ void c2r_merge(V* pl, const V* tw) {
 #ifndef RTE_EPI_UNROLL
 #define RTE_EPI_UNROLL 16
 #endif
-#ifndef RTE_PWAVES
-#define RTE_PWAVES 1
-#endif
 constexpr int kEpiUnroll = RTE_EPI_UNROLL;   // epilogue elements per thread with loads in flight
-constexpr int kPWaves = RTE_PWAVES;          // minimum waves per SIMD asked of the plane passes
 
 // Epilogue modes of the inverse pass.
 enum { EPI_MID = 0, EPI_FIRST = 1, EPI_LAST = 2, EPI_ADJ = 3, EPI_EULER = 4, EPI_APPLY = 5, EPI_SET = 6 };
@@ -748,8 +619,10 @@ __device__ __forceinline__ void block_sum2(unsigned char* smem, double a, double
   red[threadIdx.x] = a;
   red[BLOCK + threadIdx.x] = c;
   __syncthreads();
-  for (int s = BLOCK / 2; s > 0; s >>= 1) {
-    if (int(threadIdx.x) < s) {
+  int top = 1;
+  while (2 * top < BLOCK) top *= 2;   // (BLOCK need not be a power of two)
+  for (int s = top; s > 0; s >>= 1) {
+    if (int(threadIdx.x) < s && int(threadIdx.x) + s < BLOCK) {
       red[threadIdx.x] += red[threadIdx.x + s];
       red[BLOCK + threadIdx.x] += red[BLOCK + threadIdx.x + s];
     }
@@ -771,72 +644,6 @@ __device__ __forceinline__ double source_weight(const Ctl* __restrict__ ctl, int
   return ctl->qw[r * ctl->qw_cols + stage];
 }
 
-// FUSE: the stage output plane, still in LDS, is transformed forward at
-// once (x r2c + y FFT) and written as the next stage's xy spectrum to fspec
-// (which may be the spectrum just read: each workgroup owns its plane), so
-// the next stage needs no separate forward pass.
-template <typename T, int NN, int MODE, bool FUSE = false>
-__global__ void __launch_bounds__(kPBlock, kPWaves)
-k_inv_plane(const typename cplx_of<T>::type* spec, const T* vin, T* u, T* dst,
-            const T* __restrict__ sig, const T* __restrict__ q, const int* __restrict__ qflag,
-            double* __restrict__ phi_int, double* __restrict__ partial,
-            const typename cplx_of<T>::type* __restrict__ twg, int M, T h, double dt,
-            const Ctl* __restrict__ ctl, int stage, long long step1, typename cplx_of<T>::type* fspec,
-            long long bs = 0) {
-  using V = typename cplx_of<T>::type;
-  using G = GridC<NN>;
-  constexpr int n = NN, H = G::H;
-  using Lay = PlaneLayout<NN, NN>;
-  spec = slot_ptr(spec, bs);
-  vin = slot_ptr(vin, bs);
-  u = slot_ptr(u, bs);
-  dst = slot_ptr(dst, bs);
-  sig = slot_ptr(sig, bs);
-  q = slot_ptr(q, bs);
-  qflag = slot_ptr(qflag, bs);
-  phi_int = slot_ptr(phi_int, bs);
-  partial = slot_ptr(partial, bs);
-  twg = slot_ptr(twg, bs);
-  ctl = slot_ptr(ctl, bs);
-  fspec = slot_ptr(fspec, bs);
-  if (ctl->stop) return;
-  extern __shared__ __align__(16) unsigned char smem[];
-  V* tw = reinterpret_cast<V*>(smem);
-  V* pl = tw + n;
-  // logical order z-major, moment-minor: moments of one z-plane (which
-  // share the loss maps) run back to back on one XCD, ZG planes side by side
-  const int lt = xcd_tile(blockIdx.x, gridDim.x);
-  using Spec = SpecLayout<T, NN>;
-  const int zg = lt / (M * Spec::ZG), rem = lt - zg * (M * Spec::ZG);
-  const int b = rem / Spec::ZG, z = zg * Spec::ZG + rem % Spec::ZG;
-  const size_t soff = size_t(b) * Spec::MS + size_t(z) * Spec::ZS;   // the plane's spectrum
-  for (int i = threadIdx.x; i < n; i += kPBlock) tw[i] = twg[i];
-  const V* srcp = spec + soff;
-  staged_copy<n * H, kPBlock>([&](int i) { return srcp[Spec::row(i / H) + i % H]; },
-                              [&](int i, V x) { pl[Lay::pos(i / H, i % H)] = x; });
-  __syncthreads();
-  fft_batch<V, n, n, +1, H, kPBlock>(tw, Lay::yat(pl));
-  __syncthreads();
-  c2r_merge<V, T, NN, n, Lay, kPBlock>(pl, tw);
-  __syncthreads();
-  fft_batch<V, H, 2 * H, +1, n, kPBlock>(tw, Lay::xat(pl));
-  __syncthreads();
-  double acc_d = 0.0, acc_o = 0.0;
-  const bool hasq = (q != nullptr) && qflag[z];
-  const T qs = hasq ? T(source_weight(ctl, stage, step1)) : T(0);
-  epilogue<V, T, NN, n, Lay, kPBlock, MODE, FUSE>(pl, 0, b, z, vin, u, dst, sig, q, hasq, qs, phi_int, h, dt,
-                                                 acc_d, acc_o);
-  if constexpr (FUSE) {
-    __syncthreads();
-    forward_plane_lds<V, T, NN, kPBlock>(pl, tw);
-    V* fd = fspec + soff;
-    staged_copy<n * H, kPBlock>([&](int i) { return pl[Lay::pos(i / H, i % H)]; },
-                                [&](int i, V x) { fd[Spec::row(i / H) + i % H] = x; });
-  }
-  // (block_sum2 reuses the LDS: it synchronises first)
-  if ((MODE == EPI_LAST || MODE == EPI_EULER) && b == 0) block_sum2<kPBlock>(smem, acc_d, acc_o, partial + 2 * z);
-}
-
 // Inverse x transform + epilogue of RB rows per workgroup (grids whose
 // plane does not fit in LDS; the y transform ran before as a pencil pass).
 // Logical order (z group, row block, moment, z in group) so moments sharing
@@ -854,7 +661,7 @@ k_rows_inv(const typename cplx_of<T>::type* spec, const T* vin, T* u, T* dst,
            const Ctl* __restrict__ ctl, int stage, long long step1, typename cplx_of<T>::type* fspec = nullptr) {
   using V = typename cplx_of<T>::type;
   constexpr int n = NN, H = NN / 2, RB = RowShape<NN>::RB, NB = NN / RB;
-  using Lay = PlaneLayout<NN, RB>;
+  using Lay = RowsLayout<NN, RB>;
   if (ctl->stop) return;
   extern __shared__ __align__(16) unsigned char smem[];
   V* tw = reinterpret_cast<V*>(smem);
@@ -1803,9 +1610,9 @@ k_expo_blocks(typename cplx_of<T>::type* __restrict__ spec, const typename cplx_
 
 }  // namespace rte
 
-#include "rte_plane128.h"
 #include "rte_pencil.h"
 #include "rte_stream.h"
+#include "rte_plane.h"
 
 namespace rte {
 
@@ -1830,21 +1637,29 @@ void launch_pencil(hipStream_t st, const typename cplx_of<T>::type* src, typenam
 
 // ---------------------------------------------------------------- launch ---
 
-// FP32 128^3 time steps and operator applications use the register-fused
-// plane pass (rte_plane128.h); other sizes and FP64 the generic one.
-template <typename T, int NN> constexpr bool plane128() { return std::is_same<T, float>::value && NN == 128; }
-
 // Forward xy transform of `planes` real planes into the packed spectrum
-// (plane grids): the FP32 128^3 path uses the same arithmetic as the forward
-// half of its fused inverse pass.
+// (plane grids): the same arithmetic as the forward half of the fused inverse
+// pass.
 template <typename T, int NN>
 void launch_fwd_plane(hipStream_t st, const T* src, typename cplx_of<T>::type* spec,
                       const typename cplx_of<T>::type* tw, const Ctl* ctl, int planes) {
-  if constexpr (plane128<T, NN>())
-    hipLaunchKernelGGL(p128::k_fwd128<512>, dim3(planes), dim3(512), p128::kLds, st, src, spec, tw, ctl, planes);
-  else
-    hipLaunchKernelGGL((k_fwd_plane<T, NN>), dim3((planes + kFwdPlanes - 1) / kFwdPlanes), dim3(kPBlock),
-                       (plane_lds<T, NN>()), st, src, spec, tw, ctl, planes);
+  using C = pln::Cfg<T, NN>;
+  hipLaunchKernelGGL((pln::k_fwd<T, NN>), dim3(planes / C::PPW), dim3(C::BT), C::lds(), st, src, spec, tw, ctl);
+}
+
+// Inverse plane pass of all M n planes with epilogue MODE on `ns` slot rows.
+template <typename T, int NN, int MODE, bool FUSE>
+void launch_plane(const StepArgs& a, const typename cplx_of<T>::type* spec, const T* src, T* u, T* out, const T* q, int M,
+                  double hs, int stage, long long step1, unsigned ns, long long bs) {
+  using V = typename cplx_of<T>::type;
+  hipStream_t st = reinterpret_cast<hipStream_t>(a.stream);
+  const T* sig = static_cast<const T*>(a.sig);
+  const V* tw = static_cast<const V*>(a.tw);
+  const Ctl* cctl = static_cast<const Ctl*>(a.ctl);
+  V* fspec = FUSE ? static_cast<V*>(a.spec) : nullptr;
+  using C = pln::Cfg<T, NN>;
+  hipLaunchKernelGGL((pln::k_plane<T, NN, MODE, FUSE>), dim3(M * NN / C::PPW, ns), dim3(C::BT), C::lds(), st, spec, src,
+                     u, out, sig, q, a.qflag, a.phi_int, a.partial, tw, M, T(hs), a.dt, cctl, stage, step1, fspec, bs);
 }
 
 // Grids up to 128 points per axis keep a whole plane in LDS (plane passes);
@@ -1873,31 +1688,19 @@ hipError_t prepare_t(const StepArgs& a) {
     set(reinterpret_cast<const void*>(&k_pencil<T, NN, PENCIL_YFWD>), zd_lds<T, NN>());
     set(reinterpret_cast<const void*>(&k_pencil<T, NN, PENCIL_YINV>), zd_lds<T, NN>());
   } else {
-    set(reinterpret_cast<const void*>(&k_fwd_plane<T, NN>), plane_lds<T, NN>());
-    set(reinterpret_cast<const void*>(&k_inv_plane<T, NN, EPI_FIRST>), plane_lds<T, NN>());
-    set(reinterpret_cast<const void*>(&k_inv_plane<T, NN, EPI_MID>), plane_lds<T, NN>());
-    set(reinterpret_cast<const void*>(&k_inv_plane<T, NN, EPI_LAST>), plane_lds<T, NN>());
-    set(reinterpret_cast<const void*>(&k_inv_plane<T, NN, EPI_ADJ>), plane_lds<T, NN>());
-    set(reinterpret_cast<const void*>(&k_inv_plane<T, NN, EPI_EULER>), plane_lds<T, NN>());
-    set(reinterpret_cast<const void*>(&k_inv_plane<T, NN, EPI_APPLY>), plane_lds<T, NN>());
-    set(reinterpret_cast<const void*>(&k_inv_plane<T, NN, EPI_SET>), plane_lds<T, NN>());
-    set(reinterpret_cast<const void*>(&k_inv_plane<T, NN, EPI_FIRST, true>), plane_lds<T, NN>());
-    set(reinterpret_cast<const void*>(&k_inv_plane<T, NN, EPI_MID, true>), plane_lds<T, NN>());
-    set(reinterpret_cast<const void*>(&k_inv_plane<T, NN, EPI_LAST, true>), plane_lds<T, NN>());
-    set(reinterpret_cast<const void*>(&k_inv_plane<T, NN, EPI_EULER, true>), plane_lds<T, NN>());
-    if constexpr (plane128<T, NN>()) {
-      set(reinterpret_cast<const void*>(&p128::k_fwd128<512>), p128::kLds);
-      set(reinterpret_cast<const void*>(&p128::k_plane128<EPI_FIRST, false>), p128::kLds);
-      set(reinterpret_cast<const void*>(&p128::k_plane128<EPI_MID, false>), p128::kLds);
-      set(reinterpret_cast<const void*>(&p128::k_plane128<EPI_LAST, false>), p128::kLds);
-      set(reinterpret_cast<const void*>(&p128::k_plane128<EPI_ADJ, false>), p128::kLds);
-      set(reinterpret_cast<const void*>(&p128::k_plane128<EPI_EULER, false>), p128::kLds);
-      set(reinterpret_cast<const void*>(&p128::k_plane128<EPI_APPLY, false>), p128::kLds);
-      set(reinterpret_cast<const void*>(&p128::k_plane128<EPI_FIRST, true>), p128::kLds);
-      set(reinterpret_cast<const void*>(&p128::k_plane128<EPI_MID, true>), p128::kLds);
-      set(reinterpret_cast<const void*>(&p128::k_plane128<EPI_LAST, true>), p128::kLds);
-      set(reinterpret_cast<const void*>(&p128::k_plane128<EPI_EULER, true>), p128::kLds);
-    }
+    constexpr size_t lds = pln::Cfg<T, NN>::lds();
+    set(reinterpret_cast<const void*>(&pln::k_fwd<T, NN>), lds);
+    set(reinterpret_cast<const void*>(&pln::k_plane<T, NN, EPI_FIRST, false>), lds);
+    set(reinterpret_cast<const void*>(&pln::k_plane<T, NN, EPI_MID, false>), lds);
+    set(reinterpret_cast<const void*>(&pln::k_plane<T, NN, EPI_LAST, false>), lds);
+    set(reinterpret_cast<const void*>(&pln::k_plane<T, NN, EPI_ADJ, false>), lds);
+    set(reinterpret_cast<const void*>(&pln::k_plane<T, NN, EPI_EULER, false>), lds);
+    set(reinterpret_cast<const void*>(&pln::k_plane<T, NN, EPI_APPLY, false>), lds);
+    set(reinterpret_cast<const void*>(&pln::k_plane<T, NN, EPI_SET, false>), lds);
+    set(reinterpret_cast<const void*>(&pln::k_plane<T, NN, EPI_FIRST, true>), lds);
+    set(reinterpret_cast<const void*>(&pln::k_plane<T, NN, EPI_MID, true>), lds);
+    set(reinterpret_cast<const void*>(&pln::k_plane<T, NN, EPI_LAST, true>), lds);
+    set(reinterpret_cast<const void*>(&pln::k_plane<T, NN, EPI_EULER, true>), lds);
   }
   if constexpr (strm::use_stream<T, NN, N>())
     set(reinterpret_cast<const void*>(&strm::k_stream<T, NN, N>), strm::Cfg<T, NN, N>::lds());
@@ -1929,11 +1732,10 @@ void enqueue_stage(const StepArgs& a, ProfRec* pr, double hs, double sgn, const 
   const T* q = static_cast<const T*>(a.q);
   const Ctl* cctl = static_cast<const Ctl*>(a.ctl);
   const double n2 = double(NN) * NN;
-  const dim3 pblk(kPBlock), zblk(kZBlock), cblk(kCBlock);
-  const int planes = M * NN;
+  const dim3 zblk(kZBlock), cblk(kCBlock);
   const int cblocks = (NN * NN * (NN / 2) + kCBlock - 1) / kCBlock;
   const int rblocks = M * NN * (NN / RowShape<NN>::RB);
-  const size_t lp = plane_lds<T, NN>(), lr = rows_lds<T, NN>();
+  const size_t lr = rows_lds<T, NN>();
   // batched launches (plane grids, register coupling): grid rows = slots
   const unsigned ns = a.nslot > 1 ? unsigned(a.nslot) : 1u;
   const long long bs = ns > 1 ? a.sstride : 0;
@@ -1955,7 +1757,7 @@ void enqueue_stage(const StepArgs& a, ProfRec* pr, double hs, double sgn, const 
   } else if constexpr (!FUSE) {
     // (fused stages find the spectrum of src already written by the
     // previous inverse pass)
-    launch_fwd_plane<T, NN>(st, src, spec, tw, cctl, planes);
+    launch_fwd_plane<T, NN>(st, src, spec, tw, cctl, M * NN);
     rec(PROF_FWD_PLANE);
   }
   V* coupled = dspec;   // the inverse passes read the coupled spectrum from here
@@ -1983,15 +1785,8 @@ void enqueue_stage(const StepArgs& a, ProfRec* pr, double hs, double sgn, const 
                        q, a.qflag, a.phi_int, a.partial, tw, M, T(hs), a.dt, cctl, stage, step1,
                        FUSE ? spec : static_cast<V*>(nullptr));
     rec(PROF_INV_ROWS);
-  } else if constexpr (plane128<T, NN>()) {
-    hipLaunchKernelGGL((p128::k_plane128<MODE, FUSE>), dim3(planes, ns), pblk, p128::kLds, st, coupled, src, u,
-                       out, sig, q, a.qflag, a.phi_int, a.partial, tw, M, T(hs), a.dt, cctl, stage, step1,
-                       FUSE ? spec : static_cast<V*>(nullptr), bs);
-    rec(PROF_INV_PLANE);
   } else {
-    hipLaunchKernelGGL((k_inv_plane<T, NN, MODE, FUSE>), dim3(planes, ns), pblk, lp, st, coupled, src, u, out,
-                       sig, q, a.qflag, a.phi_int, a.partial, tw, M, T(hs), a.dt, cctl, stage, step1,
-                       FUSE ? spec : static_cast<V*>(nullptr), bs);
+    launch_plane<T, NN, MODE, FUSE>(a, coupled, src, u, out, q, M, hs, stage, step1, ns, bs);
     rec(PROF_INV_PLANE);
   }
 }
@@ -2014,11 +1809,10 @@ hipError_t enqueue_expo(const StepArgs& a, const OpArgs& op, ProfRec* pr) {
   const T* q = static_cast<const T*>(a.q);
   T* u = static_cast<T*>(a.u);
   const Ctl* cctl = static_cast<const Ctl*>(a.ctl);
-  const dim3 pblk(kPBlock), zblk(kZBlock);
-  const int planes = M * n;
+  const dim3 zblk(kZBlock);
   const int pencils = M * n * Z::NTILE;
   const int rblocks = M * n * (n / RowShape<NN>::RB);
-  const size_t lp = plane_lds<T, NN>(), lz = zd_lds<T, NN>(), lr = rows_lds<T, NN>();
+  const size_t lz = zd_lds<T, NN>(), lr = rows_lds<T, NN>();
   auto rec = [&](int cls) {
     if (pr && pr->count < kMaxProfLaunches) {
       (void)hipEventRecord(static_cast<hipEvent_t>(pr->ev[pr->count]), st);
@@ -2036,8 +1830,7 @@ hipError_t enqueue_expo(const StepArgs& a, const OpArgs& op, ProfRec* pr) {
       hipLaunchKernelGGL((k_pencil<T, NN, PENCIL_YFWD>), dim3(pencils), zblk, lz, st, dst, dst, tw, kv, cctl);
       rec(PROF_Y_FWD);
     } else {
-      hipLaunchKernelGGL((k_fwd_plane<T, NN>), dim3((planes + kFwdPlanes - 1) / kFwdPlanes), pblk, lp, st, src,
-                         dst, tw, cctl, planes);
+      launch_fwd_plane<T, NN>(st, src, dst, tw, cctl, M * n);
       rec(PROF_FWD_PLANE);
     }
     hipLaunchKernelGGL((k_pencil<T, NN, PENCIL_ZFWD>), dim3(pencils), zblk, lz, st, dst, dst, tw, kv, cctl);
@@ -2090,9 +1883,7 @@ hipError_t enqueue_expo(const StepArgs& a, const OpArgs& op, ProfRec* pr) {
                        0LL);
     rec(PROF_INV_ROWS);
   } else {
-    hipLaunchKernelGGL((k_inv_plane<T, NN, EPI_SET>), dim3(planes), pblk, lp, st, spec, u, u, u, sig,
-                       static_cast<const T*>(nullptr), a.qflag, a.phi_int, a.partial, tw, M, T(0), 0.0, cctl, 0,
-                       0LL, static_cast<V*>(nullptr));
+    launch_plane<T, NN, EPI_SET, false>(a, spec, u, u, u, nullptr, M, 0.0, 0, 0LL, 1, 0LL);
     rec(PROF_INV_PLANE);
   }
   return hipGetLastError();
