@@ -220,7 +220,7 @@ enum {
 };
 struct OpArgs {
   int kind;
-  int stage;         // OP_STAGE: 0..2
+  int stage;         // OP_STAGE: 0..2; OP_ADJ_STAGE: 1 for a step's last stage
   double coef;       // OP_ADJ_STAGE / OP_ADJ_GRAD: RK stage coefficient
   void* u;           // base state / accumulator
   const void* x;     // stage input
@@ -237,8 +237,9 @@ struct OpArgs {
   double sigl[kMaxOrder + 1];  // OP_EXPO: per-degree loss of the medium
   double kunit;      // OP_EXPO: 2 pi / (n dx); with count = 1 the rotation
                      // data sit in the stage buffer v
-  int fused;         // OP_STEP: the spectrum of u is in place on entry and is
-                     // left in place for the next step (plane grids)
+  int fused;         // OP_STEP / OP_STAGE / OP_ADJ_STAGE / OP_PSTEP: the spectrum of
+                     // the input is in place on entry (OP_STEP and OP_PSTEP leave
+                     // that of their result in place)
   long long step1;   // OP_STEP / OP_STAGE: 1 + the step index whose source
                      // weights apply (0: the control block's step counter)
 };

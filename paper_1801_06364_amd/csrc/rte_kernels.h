@@ -543,7 +543,7 @@ __device__ __forceinline__ void c2r_merge(V* pl, const V* tw) {
 constexpr int kEpiUnroll = RTE_EPI_UNROLL;   // epilogue elements per thread with loads in flight
 
 // Epilogue modes of the inverse pass.
-enum { EPI_MID = 0, EPI_FIRST = 1, EPI_LAST = 2, EPI_ADJ = 3, EPI_EULER = 4, EPI_APPLY = 5, EPI_SET = 6 };
+enum { EPI_MID = 0, EPI_FIRST = 1, EPI_LAST = 2, EPI_ADJ = 3, EPI_EULER = 4, EPI_APPLY = 5, EPI_SET = 6, EPI_ADJL = 7 };
 
 // Pointwise epilogue of RB rows starting at row y0 of plane (b, z), on
 // (x_{2j}, x_{2j+1}) pairs:
@@ -552,6 +552,8 @@ enum { EPI_MID = 0, EPI_FIRST = 1, EPI_LAST = 2, EPI_ADJ = 3, EPI_EULER = 4, EPI
 //     fluence moment and the partial sums of (o - u)^2 and o^2);
 //   EPI_ADJ         o = w - h Sigma_l v  -> dst, and u += o (u is the
 //     adjoint accumulator; no source term in the transposed operator);
+//   EPI_ADJL        the same without dst (a step's last transposed stage, whose
+//     o nobody reads);
 //   EPI_EULER       first and last stage at once (v = u, o -> u, bookkeeping);
 //   EPI_APPLY       o = -w + Sigma_l v -> dst with w = -S v (h = 1): the
 //     steady-state operator A v = (S + Sigma) v, for which the steady state
@@ -580,7 +582,7 @@ __device__ __forceinline__ void epilogue(V* pl, int y0, int b, int z, const T* v
     const V vv = (MODE == EPI_FIRST || MODE == EPI_EULER) ? uu : *reinterpret_cast<const V*>(vin + poff + e);
     const V ss = *reinterpret_cast<const V*>(sg + e);
     T src0 = -ss.x * vv.x, src1 = -ss.y * vv.y;
-    if (MODE != EPI_ADJ && hasq) {
+    if (MODE != EPI_ADJ && MODE != EPI_ADJL && hasq) {
       const V qq = *reinterpret_cast<const V*>(q + poff + e);
       src0 += qs * qq.x;
       src1 += qs * qq.y;
@@ -589,10 +591,11 @@ __device__ __forceinline__ void epilogue(V* pl, int y0, int b, int z, const T* v
       *reinterpret_cast<V*>(dst + poff + e) = cmk<V>(-w.x + ss.x * vv.x, -w.y + ss.y * vv.y);
       continue;
     }
-    if constexpr (MODE == EPI_ADJ) {
+    if constexpr (MODE == EPI_ADJ || MODE == EPI_ADJL) {
       const V o = cmk<V>(w.x + h * src0, w.y + h * src1);
-      *reinterpret_cast<V*>(dst + poff + e) = o;
+      if constexpr (MODE == EPI_ADJ) *reinterpret_cast<V*>(dst + poff + e) = o;
       *reinterpret_cast<V*>(u + poff + e) = cmk<V>(uu.x + o.x, uu.y + o.y);
+      if constexpr (KEEP) pl[Lay::pos(y, j)] = o;
       continue;
     }
     const V o = cmk<V>(uu.x + w.x + h * src0, uu.y + w.y + h * src1);
@@ -652,7 +655,7 @@ __device__ __forceinline__ double source_weight(const Ctl* __restrict__ ctl, int
 // written as the next stage's row spectrum to fspec (which may be the
 // spectrum just read: each workgroup owns its rows), so the next stage
 // needs no separate row pass.
-template <typename T, int NN, int MODE, bool FUSE = false>
+template <typename T, int NN, int MODE, bool FUSE>
 __global__ void __launch_bounds__(kZBlock)
 k_rows_inv(const typename cplx_of<T>::type* spec, const T* vin, T* u, T* dst,
            const T* __restrict__ sig, const T* __restrict__ q, const int* __restrict__ qflag,
@@ -789,6 +792,32 @@ k_adj_inject(T* __restrict__ lam, const long long* __restrict__ det, const doubl
   for (int p = threadIdx.x; p < ndet; p += kBlock) lam[det[p]] += T(djdr[p]);
 }
 
+// 16-byte vectors of the working precision (4 floats or 2 doubles): the
+// vector kernels stream every field with one 16-byte access per lane.
+template <typename T> struct Vec16;
+template <> struct Vec16<float> {
+  using type = float4;
+  static constexpr int W = 4;
+  static __device__ __forceinline__ double get(const float4& v, int k) {
+    return double(k == 0 ? v.x : k == 1 ? v.y : k == 2 ? v.z : v.w);
+  }
+  static __device__ __forceinline__ void set(float4& v, int k, double x) {
+    const float f = float(x);
+    if (k == 0) v.x = f;
+    else if (k == 1) v.y = f;
+    else if (k == 2) v.z = f;
+    else v.w = f;
+  }
+};
+template <> struct Vec16<double> {
+  using type = double2;
+  static constexpr int W = 2;
+  static __device__ __forceinline__ double get(const double2& v, int k) { return k == 0 ? v.x : v.y; }
+  static __device__ __forceinline__ void set(double2& v, int k, double x) {
+    if (k == 0) v.x = x;
+    else v.y = x;
+  }
+};
 // ------------------------------------------- media and states from HBM ---
 
 // Per-degree loss inside the real domain, Sigma_l = mu_a + mu_s (1 - g^l),
@@ -821,26 +850,47 @@ k_set_state_f64(T* __restrict__ u, const double* __restrict__ psi, long long giv
 }
 
 // Runaway-growth threshold 1e16 (E + source_term + 1e-300) with E the
-// (2l+1)-weighted energy of u (one workgroup, fixed partition and tree:
-// deterministic); the same rule as the host-side threshold of a state set
-// from host memory.
+// (2l+1)-weighted energy of u; the same rule as the host-side threshold of a
+// state set from host memory. Block partial sums, then one block over them
+// (fixed partition and tree: deterministic). Bound by reading u once: 57 MB
+// (96^3 P_3 FP32) in 12 us with kGrowthBlocks blocks; a single workgroup took
+// 3.8 ms. The partial sums sit in the per-plane partials of the time step
+// (n^2 pairs, n >= 16), which hold nothing between steps.
+constexpr int kGrowthBlocks = 512;
 template <typename T>
-__global__ void __launch_bounds__(1024)
-k_growth_limit(const T* __restrict__ u, int M, long long V, double source_term, Ctl* __restrict__ ctl) {
-  __shared__ double red[1024];
+__global__ void __launch_bounds__(kBlock)
+k_growth_sums(const T* __restrict__ u, int M, long long V, double* __restrict__ partial) {
+  using VT = Vec16<T>;
+  using X = typename VT::type;
+  __shared__ double red[kBlock];
+  const long long nv = V / VT::W;   // (n is a multiple of 16)
   double e = 0.0;
   for (int a = 0; a < M; ++a) {
-    const double wt = double(2 * isqrt_c(a) + 1);
+    const X* ua = reinterpret_cast<const X*>(u + (long long)a * V);
     double s = 0.0;
-    for (long long i = threadIdx.x; i < V; i += 1024) {
-      const double x = double(u[(long long)a * V + i]);
-      s += x * x;
+    for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < nv; i += (long long)kGrowthBlocks * kBlock) {
+      const X x = ua[i];
+#pragma unroll
+      for (int k = 0; k < VT::W; ++k) s += VT::get(x, k) * VT::get(x, k);
     }
-    e += wt * s;
+    e += double(2 * isqrt_c(a) + 1) * s;
   }
   red[threadIdx.x] = e;
   __syncthreads();
-  for (int w = 512; w > 0; w >>= 1) {
+  for (int w = kBlock / 2; w > 0; w >>= 1) {
+    if (int(threadIdx.x) < w) red[threadIdx.x] += red[threadIdx.x + w];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
+}
+
+template <typename T>   // instantiated per working precision (one copy per translation unit)
+__global__ void __launch_bounds__(kGrowthBlocks)
+k_growth_limit(const double* __restrict__ partial, double source_term, Ctl* __restrict__ ctl) {
+  __shared__ double red[kGrowthBlocks];
+  red[threadIdx.x] = partial[threadIdx.x];
+  __syncthreads();
+  for (int w = kGrowthBlocks / 2; w > 0; w >>= 1) {
     if (int(threadIdx.x) < w) red[threadIdx.x] += red[threadIdx.x + w];
     __syncthreads();
   }
@@ -860,32 +910,6 @@ k_growth_limit(const T* __restrict__ u, int M, long long V, double source_term, 
 constexpr int kDotBlocks = 1024;
 constexpr int kMaxBasis = 32;
 
-// 16-byte vectors of the working precision (4 floats or 2 doubles): the
-// vector kernels stream every field with one 16-byte access per lane.
-template <typename T> struct Vec16;
-template <> struct Vec16<float> {
-  using type = float4;
-  static constexpr int W = 4;
-  static __device__ __forceinline__ double get(const float4& v, int k) {
-    return double(k == 0 ? v.x : k == 1 ? v.y : k == 2 ? v.z : v.w);
-  }
-  static __device__ __forceinline__ void set(float4& v, int k, double x) {
-    const float f = float(x);
-    if (k == 0) v.x = f;
-    else if (k == 1) v.y = f;
-    else if (k == 2) v.z = f;
-    else v.w = f;
-  }
-};
-template <> struct Vec16<double> {
-  using type = double2;
-  static constexpr int W = 2;
-  static __device__ __forceinline__ double get(const double2& v, int k) { return k == 0 ? v.x : v.y; }
-  static __device__ __forceinline__ void set(double2& v, int k, double x) {
-    if (k == 0) v.x = x;
-    else v.y = x;
-  }
-};
 constexpr int kVecGroup = 8;   // basis vectors whose loads are in flight together
 
 template <typename T>
@@ -1674,33 +1698,29 @@ hipError_t prepare_t(const StepArgs& a) {
   };
   if constexpr (split_planes<NN>()) {
     set(reinterpret_cast<const void*>(&k_rows_fwd<T, NN>), rows_lds<T, NN>());
-    set(reinterpret_cast<const void*>(&k_rows_inv<T, NN, EPI_FIRST>), rows_lds<T, NN>());
-    set(reinterpret_cast<const void*>(&k_rows_inv<T, NN, EPI_MID>), rows_lds<T, NN>());
-    set(reinterpret_cast<const void*>(&k_rows_inv<T, NN, EPI_LAST>), rows_lds<T, NN>());
-    set(reinterpret_cast<const void*>(&k_rows_inv<T, NN, EPI_ADJ>), rows_lds<T, NN>());
-    set(reinterpret_cast<const void*>(&k_rows_inv<T, NN, EPI_EULER>), rows_lds<T, NN>());
-    set(reinterpret_cast<const void*>(&k_rows_inv<T, NN, EPI_APPLY>), rows_lds<T, NN>());
-    set(reinterpret_cast<const void*>(&k_rows_inv<T, NN, EPI_SET>), rows_lds<T, NN>());
+    set(reinterpret_cast<const void*>(&k_rows_inv<T, NN, EPI_MID, false>), rows_lds<T, NN>());
+    set(reinterpret_cast<const void*>(&k_rows_inv<T, NN, EPI_APPLY, false>), rows_lds<T, NN>());
+    set(reinterpret_cast<const void*>(&k_rows_inv<T, NN, EPI_SET, false>), rows_lds<T, NN>());
     set(reinterpret_cast<const void*>(&k_rows_inv<T, NN, EPI_FIRST, true>), rows_lds<T, NN>());
     set(reinterpret_cast<const void*>(&k_rows_inv<T, NN, EPI_MID, true>), rows_lds<T, NN>());
     set(reinterpret_cast<const void*>(&k_rows_inv<T, NN, EPI_LAST, true>), rows_lds<T, NN>());
     set(reinterpret_cast<const void*>(&k_rows_inv<T, NN, EPI_EULER, true>), rows_lds<T, NN>());
+    set(reinterpret_cast<const void*>(&k_rows_inv<T, NN, EPI_ADJ, true>), rows_lds<T, NN>());
+    set(reinterpret_cast<const void*>(&k_rows_inv<T, NN, EPI_ADJL, false>), rows_lds<T, NN>());
     set(reinterpret_cast<const void*>(&k_pencil<T, NN, PENCIL_YFWD>), zd_lds<T, NN>());
     set(reinterpret_cast<const void*>(&k_pencil<T, NN, PENCIL_YINV>), zd_lds<T, NN>());
   } else {
     constexpr size_t lds = pln::Cfg<T, NN>::lds();
     set(reinterpret_cast<const void*>(&pln::k_fwd<T, NN>), lds);
-    set(reinterpret_cast<const void*>(&pln::k_plane<T, NN, EPI_FIRST, false>), lds);
     set(reinterpret_cast<const void*>(&pln::k_plane<T, NN, EPI_MID, false>), lds);
-    set(reinterpret_cast<const void*>(&pln::k_plane<T, NN, EPI_LAST, false>), lds);
-    set(reinterpret_cast<const void*>(&pln::k_plane<T, NN, EPI_ADJ, false>), lds);
-    set(reinterpret_cast<const void*>(&pln::k_plane<T, NN, EPI_EULER, false>), lds);
     set(reinterpret_cast<const void*>(&pln::k_plane<T, NN, EPI_APPLY, false>), lds);
     set(reinterpret_cast<const void*>(&pln::k_plane<T, NN, EPI_SET, false>), lds);
     set(reinterpret_cast<const void*>(&pln::k_plane<T, NN, EPI_FIRST, true>), lds);
     set(reinterpret_cast<const void*>(&pln::k_plane<T, NN, EPI_MID, true>), lds);
     set(reinterpret_cast<const void*>(&pln::k_plane<T, NN, EPI_LAST, true>), lds);
     set(reinterpret_cast<const void*>(&pln::k_plane<T, NN, EPI_EULER, true>), lds);
+    set(reinterpret_cast<const void*>(&pln::k_plane<T, NN, EPI_ADJ, true>), lds);
+    set(reinterpret_cast<const void*>(&pln::k_plane<T, NN, EPI_ADJL, false>), lds);
   }
   if constexpr (strm::use_stream<T, NN, N>())
     set(reinterpret_cast<const void*>(&strm::k_stream<T, NN, N>), strm::Cfg<T, NN, N>::lds());
@@ -1718,8 +1738,11 @@ template <int NN> constexpr int partial_count() {
 
 // One stage: out = MODE-epilogue of (u, src) with the streaming term
 // sgn * a h c (-B.grad src) (sgn = -1 gives the transposed streaming).
-template <typename T, int NN, int N, int MODE, bool FUSE = false>
-void enqueue_stage(const StepArgs& a, ProfRec* pr, double hs, double sgn, const T* src, T* u, T* out,
+// have: the spectrum of src (xy on plane grids, x on split grids) is in place
+// in a.spec, left there by the stage before; FUSE: the stage leaves that of
+// its output there.
+template <typename T, int NN, int N, int MODE, bool FUSE>
+void enqueue_stage(const StepArgs& a, ProfRec* pr, double hs, double sgn, const T* src, T* u, T* out, bool have,
                    int stage = 0, long long step1 = 0) {
   using V = typename cplx_of<T>::type;
   constexpr int M = (N + 1) * (N + 1);
@@ -1746,17 +1769,13 @@ void enqueue_stage(const StepArgs& a, ProfRec* pr, double hs, double sgn, const 
     }
   };
   if constexpr (split_planes<NN>()) {
-    // (fused stages find the row spectrum of src already written by the
-    // previous inverse row pass)
-    if constexpr (!FUSE) {
+    if (!have) {
       hipLaunchKernelGGL((k_rows_fwd<T, NN>), dim3(rblocks), zblk, lr, st, src, spec, tw, cctl);
       rec(PROF_FWD_ROWS);
     }
     launch_pencil<T, NN, PENCIL_YFWD>(st, spec, spec, tw, kv, cctl, M);
     rec(PROF_Y_FWD);
-  } else if constexpr (!FUSE) {
-    // (fused stages find the spectrum of src already written by the
-    // previous inverse pass)
+  } else if (!have) {
     launch_fwd_plane<T, NN>(st, src, spec, tw, cctl, M * NN);
     rec(PROF_FWD_PLANE);
   }
@@ -1878,7 +1897,7 @@ hipError_t enqueue_expo(const StepArgs& a, const OpArgs& op, ProfRec* pr) {
   if constexpr (split_planes<NN>()) {
     hipLaunchKernelGGL((k_pencil<T, NN, PENCIL_YINV>), dim3(pencils), zblk, lz, st, spec, spec, tw, kv, cctl);
     rec(PROF_Y_INV);
-    hipLaunchKernelGGL((k_rows_inv<T, NN, EPI_SET>), dim3(rblocks), zblk, lr, st, spec, u, u, u, sig,
+    hipLaunchKernelGGL((k_rows_inv<T, NN, EPI_SET, false>), dim3(rblocks), zblk, lr, st, spec, u, u, u, sig,
                        static_cast<const T*>(nullptr), a.qflag, a.phi_int, a.partial, tw, M, T(0), 0.0, cctl, 0,
                        0LL);
     rec(PROF_INV_ROWS);
@@ -1907,30 +1926,18 @@ hipError_t enqueue_t(const StepArgs& a, const OpArgs& op, ProfRec* pr) {
         pr->count = 0;
       }
       const long long s1 = op.step1;
-      bool done = false;
-      if (op.fused) {
-        // the spectrum of u (xy on plane grids, x on split grids) is in
-        // place on entry; every inverse pass leaves that of its output for
-        // the next stage (the last one that of the new u, for the next step)
-        if (a.scheme == 1) {
-          enqueue_stage<T, NN, N, EPI_EULER, true>(a, pr, hc, 1.0, u, u, u, 0, s1);
-        } else {
-          enqueue_stage<T, NN, N, EPI_FIRST, true>(a, pr, kRkAlpha[0] * hc, 1.0, u, u, v, 0, s1);
-          enqueue_stage<T, NN, N, EPI_MID, true>(a, pr, kRkAlpha[1] * hc, 1.0, v, u, v, 1, s1);
-          enqueue_stage<T, NN, N, EPI_MID, true>(a, pr, kRkAlpha[2] * hc, 1.0, v, u, v, 2, s1);
-          enqueue_stage<T, NN, N, EPI_LAST, true>(a, pr, kRkAlpha[3] * hc, 1.0, v, u, u, 3, s1);
-        }
-        done = true;
-      }
-      if (done) {
-      } else if (a.scheme == 1) {
+      // with op.fused the spectrum of u is in place on entry; every inverse
+      // pass leaves that of its output for the next stage (the last one that
+      // of the new u, for the next step)
+      const bool have = op.fused != 0;
+      if (a.scheme == 1) {
         // forward Euler (eq. 11 with the sign reading): u <- u + dt f(u)
-        enqueue_stage<T, NN, N, EPI_EULER>(a, pr, hc, 1.0, u, u, u, 0, s1);
+        enqueue_stage<T, NN, N, EPI_EULER, true>(a, pr, hc, 1.0, u, u, u, have, 0, s1);
       } else {
-        enqueue_stage<T, NN, N, EPI_FIRST>(a, pr, kRkAlpha[0] * hc, 1.0, u, u, v, 0, s1);
-        enqueue_stage<T, NN, N, EPI_MID>(a, pr, kRkAlpha[1] * hc, 1.0, v, u, v, 1, s1);
-        enqueue_stage<T, NN, N, EPI_MID>(a, pr, kRkAlpha[2] * hc, 1.0, v, u, v, 2, s1);
-        enqueue_stage<T, NN, N, EPI_LAST>(a, pr, kRkAlpha[3] * hc, 1.0, v, u, u, 3, s1);
+        enqueue_stage<T, NN, N, EPI_FIRST, true>(a, pr, kRkAlpha[0] * hc, 1.0, u, u, v, have, 0, s1);
+        enqueue_stage<T, NN, N, EPI_MID, true>(a, pr, kRkAlpha[1] * hc, 1.0, v, u, v, true, 1, s1);
+        enqueue_stage<T, NN, N, EPI_MID, true>(a, pr, kRkAlpha[2] * hc, 1.0, v, u, v, true, 2, s1);
+        enqueue_stage<T, NN, N, EPI_LAST, true>(a, pr, kRkAlpha[3] * hc, 1.0, v, u, u, true, 3, s1);
       }
       const unsigned ns = a.nslot > 1 ? unsigned(a.nslot) : 1u;
       hipLaunchKernelGGL((k_end_step<T>), dim3(1, ns), dim3(kBlock), 0, st, u, a.det, a.ndet, a.readings, a.resid,
@@ -1944,19 +1951,29 @@ hipError_t enqueue_t(const StepArgs& a, const OpArgs& op, ProfRec* pr) {
     }
     case OP_STAGE: {
       // forward stage op.stage (0..2) of the nested RK4 form from base state
-      // op.u with stage input op.x, writing op.y (no bookkeeping)
+      // op.u with stage input op.x, writing op.y (no bookkeeping); op.fused:
+      // the spectrum of the input is in place, stages 0 and 1 leave that of
+      // their output
       const int s = op.stage;
       const T* xin = static_cast<const T*>(op.x);
       T* u = static_cast<T*>(op.u);
       T* out = static_cast<T*>(op.y);
-      if (s == 0) enqueue_stage<T, NN, N, EPI_FIRST>(a, nullptr, kRkAlpha[0] * hc, 1.0, u, u, out, 0, op.step1);
-      else enqueue_stage<T, NN, N, EPI_MID>(a, nullptr, kRkAlpha[s] * hc, 1.0, xin, u, out, s, op.step1);
+      const bool have = op.fused != 0;
+      if (s == 0) enqueue_stage<T, NN, N, EPI_FIRST, true>(a, nullptr, kRkAlpha[0] * hc, 1.0, u, u, out, have, 0, op.step1);
+      else if (s == 1)
+        enqueue_stage<T, NN, N, EPI_MID, true>(a, nullptr, kRkAlpha[1] * hc, 1.0, xin, u, out, have, 1, op.step1);
+      else enqueue_stage<T, NN, N, EPI_MID, false>(a, nullptr, kRkAlpha[2] * hc, 1.0, xin, u, out, have, 2, op.step1);
       break;
     }
     case OP_ADJ_STAGE: {
-      // xs_out = coef h F~(xs_in) with the streaming sign flipped, acc += xs_out
-      enqueue_stage<T, NN, N, EPI_ADJ>(a, nullptr, op.coef * hc, -1.0, static_cast<const T*>(op.x),
-                                       static_cast<T*>(op.u), static_cast<T*>(op.y));
+      // xs_out = coef h F~(xs_in) with the streaming sign flipped, acc += xs_out;
+      // op.fused: the spectrum of xs_in is in place; left behind is that of
+      // xs_out. A step's last stage (op.stage = 1) writes acc only
+      T* x = static_cast<T*>(const_cast<void*>(op.x));
+      T* acc = static_cast<T*>(op.u);
+      T* out = static_cast<T*>(op.y);
+      if (op.stage == 1) enqueue_stage<T, NN, N, EPI_ADJL, false>(a, nullptr, op.coef * hc, -1.0, x, acc, out, op.fused != 0);
+      else enqueue_stage<T, NN, N, EPI_ADJ, true>(a, nullptr, op.coef * hc, -1.0, x, acc, out, op.fused != 0);
       break;
     }
     case OP_ADJ_GRAD: {
@@ -1968,8 +1985,8 @@ hipError_t enqueue_t(const StepArgs& a, const OpArgs& op, ProfRec* pr) {
     }
     case OP_APPLY: {
       // y = (S + Sigma) x
-      enqueue_stage<T, NN, N, EPI_APPLY>(a, nullptr, 1.0, 1.0, static_cast<const T*>(op.x),
-                                         static_cast<T*>(op.y), static_cast<T*>(op.y));
+      enqueue_stage<T, NN, N, EPI_APPLY, false>(a, nullptr, 1.0, 1.0, static_cast<const T*>(op.x),
+                                                static_cast<T*>(op.y), static_cast<T*>(op.y), false);
       break;
     }
     case OP_WDOTS: {
@@ -2009,8 +2026,11 @@ hipError_t enqueue_t(const StepArgs& a, const OpArgs& op, ProfRec* pr) {
       break;
     }
     case OP_GROWTH: {
-      hipLaunchKernelGGL((k_growth_limit<T>), dim3(1), dim3(1024), 0, st, static_cast<const T*>(a.u), M, nvox,
-                         op.scale, static_cast<Ctl*>(a.ctl));
+      static_assert(2 * 16 * 16 >= kGrowthBlocks, "the partials of the smallest grid hold the block sums");
+      hipLaunchKernelGGL((k_growth_sums<T>), dim3(kGrowthBlocks), dim3(kBlock), 0, st, static_cast<const T*>(a.u), M,
+                         nvox, a.partial);
+      hipLaunchKernelGGL((k_growth_limit<T>), dim3(1), dim3(kGrowthBlocks), 0, st, a.partial, op.scale,
+                         static_cast<Ctl*>(a.ctl));
       break;
     }
     case OP_GM_UPDATE: {
@@ -2042,16 +2062,18 @@ hipError_t enqueue_t(const StepArgs& a, const OpArgs& op, ProfRec* pr) {
       else return hipErrorInvalidValue;
     case OP_PSTEP: {
       // one step of the handle's scheme on op.u in place (op.y holds the
-      // stage values); the source is the one in a (null: none)
+      // stage values); the source is the one in a (null: none); op.fused: the
+      // spectrum of op.u is in place (a step leaves that of its result)
       T* x = static_cast<T*>(op.u);
       T* tmp = static_cast<T*>(op.y);
+      const bool have = op.fused != 0;
       if (a.scheme == 1) {
-        enqueue_stage<T, NN, N, EPI_FIRST>(a, nullptr, hc, 1.0, x, x, x);
+        enqueue_stage<T, NN, N, EPI_FIRST, true>(a, nullptr, hc, 1.0, x, x, x, have);
       } else {
-        enqueue_stage<T, NN, N, EPI_FIRST>(a, nullptr, kRkAlpha[0] * hc, 1.0, x, x, tmp);
-        enqueue_stage<T, NN, N, EPI_MID>(a, nullptr, kRkAlpha[1] * hc, 1.0, tmp, x, tmp);
-        enqueue_stage<T, NN, N, EPI_MID>(a, nullptr, kRkAlpha[2] * hc, 1.0, tmp, x, tmp);
-        enqueue_stage<T, NN, N, EPI_MID>(a, nullptr, kRkAlpha[3] * hc, 1.0, tmp, x, x);
+        enqueue_stage<T, NN, N, EPI_FIRST, true>(a, nullptr, kRkAlpha[0] * hc, 1.0, x, x, tmp, have);
+        enqueue_stage<T, NN, N, EPI_MID, true>(a, nullptr, kRkAlpha[1] * hc, 1.0, tmp, x, tmp, true);
+        enqueue_stage<T, NN, N, EPI_MID, true>(a, nullptr, kRkAlpha[2] * hc, 1.0, tmp, x, tmp, true);
+        enqueue_stage<T, NN, N, EPI_MID, true>(a, nullptr, kRkAlpha[3] * hc, 1.0, tmp, x, x, true);
       }
       break;
     }

@@ -1000,9 +1000,13 @@ int adjoint_run(rte_handle* h, int64_t steps, int64_t every, void* adj_ws, size_
     o.gmus = reinterpret_cast<double*>(w + A.gmus);
     op(R, o);
   };
-  auto adj_stage = [&](const void* x, void* y, double coef) {
+  // have: the stage before left the spectrum of x in place; last: nobody
+  // reads y, which is then not written
+  auto adj_stage = [&](const void* x, void* y, double coef, bool have, bool last) {
     OpArgs o{};
     o.kind = OP_ADJ_STAGE;
+    o.fused = have;
+    o.stage = last;
     o.x = x;
     o.y = y;
     o.u = w + A.lam;
@@ -1013,6 +1017,7 @@ int adjoint_run(rte_handle* h, int64_t steps, int64_t every, void* adj_ws, size_
     OpArgs o{};
     o.kind = OP_STAGE;
     o.stage = s;
+    o.fused = s > 0;
     o.step1 = s0 + nn + 1;
     o.u = const_cast<void*>(un);
     o.x = x;
@@ -1033,6 +1038,7 @@ int adjoint_run(rte_handle* h, int64_t steps, int64_t every, void* adj_ws, size_
       S.u = next;
       OpArgs o{};
       o.kind = OP_STEP;
+      o.fused = nn > n0;   // the copy has the spectrum that the step before left
       o.step1 = s0 + nn + 1;
       op(S, o);
     }
@@ -1041,7 +1047,7 @@ int adjoint_run(rte_handle* h, int64_t steps, int64_t every, void* adj_ws, size_
       if (h->args.scheme == RTE_EULER) {
         // u' = u + h F(u): lam <- lam + h F^T lam, gradient term (lam, u)
         grad(w + A.lam, un, 1.0);
-        adj_stage(w + A.lam, w + A.xa, 1.0);
+        adj_stage(w + A.lam, w + A.xa, 1.0, false, true);
         if (nn >= 1) inject(nn - 1);
         continue;
       }
@@ -1051,13 +1057,13 @@ int adjoint_run(rte_handle* h, int64_t steps, int64_t every, void* adj_ws, size_
       // transposed nested stages (coefficients 1, 1/2, 1/3, 1/4), each
       // preceded by the gradient term of its forward counterpart
       grad(w + A.lam, w + A.v3, 1.0);
-      adj_stage(w + A.lam, w + A.xa, 1.0);
+      adj_stage(w + A.lam, w + A.xa, 1.0, false, false);
       grad(w + A.xa, w + A.v2, 0.5);
-      adj_stage(w + A.xa, w + A.xb, 0.5);
+      adj_stage(w + A.xa, w + A.xb, 0.5, true, false);
       grad(w + A.xb, w + A.v1, 1.0 / 3.0);
-      adj_stage(w + A.xb, w + A.xa, 1.0 / 3.0);
+      adj_stage(w + A.xb, w + A.xa, 1.0 / 3.0, true, false);
       grad(w + A.xa, un, 0.25);
-      adj_stage(w + A.xa, w + A.xb, 0.25);
+      adj_stage(w + A.xa, w + A.xb, 0.25, true, true);
       if (nn >= 1) inject(nn - 1);
     }
   }
@@ -1207,6 +1213,7 @@ int gmres_run(rte_handle* h, int32_t restart, int64_t max_iters, double tol, int
     for (int k = 0; k < K; ++k) {
       OpArgs o{};
       o.kind = OP_PSTEP;
+      o.fused = k > 0;   // the step before left the spectrum of x
       o.u = x;
       o.y = tmp;
       op(args, o);

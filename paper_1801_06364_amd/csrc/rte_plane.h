@@ -361,6 +361,7 @@ k_plane(const typename cplx_of<T>::type* spec, const T* vin, T* u, T* dst, const
   const int pr = C::PPW == 1 ? 0 : yy / n, y = yy - pr * n;
   V* row = pls + pr * C::PSIZE + y * C::PITCH;
   constexpr bool kLast = (MODE == EPI_LAST || MODE == EPI_EULER);
+  constexpr bool kAdj = (MODE == EPI_ADJ || MODE == EPI_ADJL);
   constexpr bool kSrc = kLast || MODE == EPI_FIRST || MODE == EPI_MID;
   V c[C::PR];
   {
@@ -461,14 +462,14 @@ k_plane(const typename cplx_of<T>::type* spec, const T* vin, T* u, T* dst, const
             o.v[w] = x;
           } else {
             T s = -ss[k].v[w] * vv[k].v[w];
-            if constexpr (MODE != EPI_ADJ) s += of(pq, pp[k]) * qq[k].v[w];
+            if constexpr (!kAdj) s += of(pq, pp[k]) * qq[k].v[w];
             if constexpr (MODE == EPI_APPLY) o.v[w] = -x + ss[k].v[w] * vv[k].v[w];
-            else if constexpr (MODE == EPI_ADJ) o.v[w] = x + h * s;
+            else if constexpr (kAdj) o.v[w] = x + h * s;
             else o.v[w] = uu[k].v[w] + x + h * s;
           }
         }
-        *reinterpret_cast<I*>(dst + po[k]) = o;
-        if constexpr (MODE == EPI_ADJ) {
+        if constexpr (MODE != EPI_ADJL) *reinterpret_cast<I*>(dst + po[k]) = o;
+        if constexpr (kAdj) {
           I a;
 #pragma unroll
           for (int w = 0; w < 2 * CW; ++w) a.v[w] = uu[k].v[w] + o.v[w];

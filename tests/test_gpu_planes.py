@@ -50,3 +50,33 @@ def test_planes_against_oracle(n, N, prec):
     res = s.residuals()
     s.close()
     assert np.allclose(res, ref["residual"], rtol=1e-9 if prec == "f64" else 1e-3, atol=0.0)
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("n,N", [(16, 0), (16, 3), (48, 2), (64, 5)])
+def test_growth_threshold_of_a_device_state(n, N, prec):
+    """The runaway-growth threshold of a state set from device memory (block
+    sums, then one block; fewer vectors than threads at 16^3) equals that of
+    the same state set from the host: sums of at most 64 n^3 positive FP64
+    terms in two orders, so within (64 n^3) 2^-53 < 2e-9 of each other. The
+    snapshot carries it after the 32 bytes magic, hash, step, flags."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import struct
+
+    from paper_1801_06364_amd.rte import Solver
+    print(f"\n[growth] n={n} N={N} {prec}", flush=True)
+    M = (N + 1) ** 2
+    psi = np.random.default_rng(n + N).standard_normal((M, n, n, n)).astype(np.float32).astype(np.float64)
+    flat = np.full((n, n, n), 0.5)
+    s = Solver(n, N, 0.25, 0.3, 0.0, flat, flat, flat, precision=prec, stream=torch.cuda.Stream())
+    limits = []
+    s.set_state(psi)
+    limits.append(struct.unpack_from("d", s.snapshot(), 32)[0])
+    s.set_state_device(torch.from_numpy(psi.ravel()).cuda())
+    limits.append(struct.unpack_from("d", s.snapshot(), 32)[0])
+    s.close()
+    w = np.repeat(2 * np.arange(N + 1) + 1, 2 * np.arange(N + 1) + 1)
+    assert abs(limits[0] / (1e16 * (w * (psi ** 2).reshape(M, -1).sum(1)).sum()) - 1) <= 2e-9
+    assert abs(limits[1] / limits[0] - 1) <= 2e-9
