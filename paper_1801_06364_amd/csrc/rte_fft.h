@@ -1,5 +1,5 @@
 // Device building blocks for the P_N stepper on gfx950: complex helpers,
-// radix-2/3/4/8 butterflies and a Stockham auto-sort FFT of compile-time
+// radix-2/3/4/6/8/12/16/24 butterflies and a Stockham auto-sort FFT of compile-time
 // length executed by a group of P lanes of one wavefront on data staged in
 // LDS.
 //
@@ -178,6 +178,56 @@ template <typename V, int DIR> struct Bfly<V, 16, DIR> {
       for (int q2 = 0; q2 < 4; ++q2) v[q1 + 4 * q2] = t[q2];
     }
   }
+};
+
+// cos(t pi / 12) from the closed forms of the multiples of 15 degrees
+__host__ __device__ constexpr double cos_pi12(int t) {
+  constexpr double c[7] = {1.0, 0.96592582628906828675, 0.86602540378443864676, 0.70710678118654752440,
+                           0.5, 0.25881904510252076235, 0.0};
+  t = ((t % 24) + 24) % 24;
+  if (t > 12) t = 24 - t;
+  return t <= 6 ? c[t] : -c[12 - t];
+}
+
+// exp(DIR 2 pi i t / 24)
+template <typename V, int DIR> __device__ __forceinline__ V w24(int t) {
+  using T = decltype(V::x);
+  return cmk<V>(T(cos_pi12(t)), T(DIR) * T(cos_pi12(6 - t)));
+}
+
+// DFT of R = A B points in registers (A, B coprime or not): r = a + A b,
+// q = c + B d: radix B over b for each a, twiddles exp(DIR 2 pi i a c / R),
+// radix A over a. R divides 24, so every twiddle is a closed form.
+template <typename V, int A, int B, int DIR> __device__ __forceinline__ void dft_ab(V* x) {
+  V y[A][B];
+#pragma unroll
+  for (int a = 0; a < A; ++a) {
+#pragma unroll
+    for (int b = 0; b < B; ++b) y[a][b] = x[a + A * b];
+    Bfly<V, B, DIR>::run(y[a]);
+  }
+#pragma unroll
+  for (int a = 1; a < A; ++a)
+#pragma unroll
+    for (int c = 1; c < B; ++c) y[a][c] = cmul(y[a][c], w24<V, DIR>(24 / (A * B) * a * c));
+#pragma unroll
+  for (int c = 0; c < B; ++c) {
+    V z[A];
+#pragma unroll
+    for (int a = 0; a < A; ++a) z[a] = y[a][c];
+    Bfly<V, A, DIR>::run(z);
+#pragma unroll
+    for (int d = 0; d < A; ++d) x[c + B * d] = z[d];
+  }
+}
+template <typename V, int DIR> struct Bfly<V, 6, DIR> {
+  static __device__ __forceinline__ void run(V* v) { dft_ab<V, 2, 3, DIR>(v); }
+};
+template <typename V, int DIR> struct Bfly<V, 12, DIR> {
+  static __device__ __forceinline__ void run(V* v) { dft_ab<V, 3, 4, DIR>(v); }
+};
+template <typename V, int DIR> struct Bfly<V, 24, DIR> {
+  static __device__ __forceinline__ void run(V* v) { dft_ab<V, 3, 8, DIR>(v); }
 };
 
 // Element accessors. An FFT pass addresses element i of FFT f through an

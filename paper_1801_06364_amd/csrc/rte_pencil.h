@@ -56,15 +56,6 @@ template <int DIR> __device__ __forceinline__ float2 tw_dir(float2 w) {
 // x <- x * (i k / n)
 __device__ __forceinline__ float2 times_ik(float2 x, float k) { return cmk<float2>(-k * x.y, k * x.x); }
 
-// cos(t pi / 12) from the closed forms of the multiples of 15 degrees
-__host__ __device__ constexpr double cos_pi12(int t) {
-  constexpr double c[7] = {1.0, 0.96592582628906828675, 0.86602540378443864676, 0.70710678118654752440,
-                           0.5, 0.25881904510252076235, 0.0};
-  t = ((t % 24) + 24) % 24;
-  if (t > 12) t = 24 - t;
-  return t <= 6 ? c[t] : -c[12 - t];
-}
-
 template <int NN, int MODE>
 __global__ void __launch_bounds__(Shape<NN>::THREADS)
 k_pencil_reg(const float2* src, float2* dst,   // may alias (in place)

@@ -87,54 +87,6 @@ template <typename T, int NN> struct Cfg {
   }
 };
 
-template <typename V, int DIR> __device__ __forceinline__ void dft6(V* x) {
-  // r = a + 2 b, q = c + 3 d: radix 3 over b, exp(DIR 2 pi i a c / 6), radix 2
-  using T = decltype(V::x);
-  V y[2][3];
-#pragma unroll
-  for (int a = 0; a < 2; ++a) {
-#pragma unroll
-    for (int b = 0; b < 3; ++b) y[a][b] = x[a + 2 * b];
-    Bfly<V, 3, DIR>::run(y[a]);
-  }
-#pragma unroll
-  for (int c = 1; c < 3; ++c)
-    y[1][c] = cmul(y[1][c], cmk<V>(T(pen::cos_pi12(4 * c)), T(DIR) * T(pen::cos_pi12(6 - 4 * c))));
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    x[c] = cadd(y[0][c], y[1][c]);
-    x[c + 3] = csub(y[0][c], y[1][c]);
-  }
-}
-// 24 = 8 x 3: r = a + 3 b, q = c + 8 d
-template <typename V, int DIR> __device__ __forceinline__ void dft24(V* x) {
-  using T = decltype(V::x);
-  V y[3][8];
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-#pragma unroll
-    for (int b = 0; b < 8; ++b) y[a][b] = x[a + 3 * b];
-    Bfly<V, 8, DIR>::run(y[a]);
-  }
-#pragma unroll
-  for (int a = 1; a < 3; ++a)
-#pragma unroll
-    for (int c = 1; c < 8; ++c)
-      y[a][c] = cmul(y[a][c], cmk<V>(T(pen::cos_pi12(a * c)), T(DIR) * T(pen::cos_pi12(6 - a * c))));
-#pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    V z[3] = {y[0][c], y[1][c], y[2][c]};
-    Bfly<V, 3, DIR>::run(z);
-#pragma unroll
-    for (int d = 0; d < 3; ++d) x[c + 8 * d] = z[d];
-  }
-}
-template <typename V, int R, int DIR> __device__ __forceinline__ void dft(V* x) {
-  if constexpr (R == 6) dft6<V, DIR>(x);
-  else if constexpr (R == 24) dft24<V, DIR>(x);
-  else strm::dft<V, R, DIR>(x);
-}
-
 template <int DIR, typename V> __device__ __forceinline__ V twd(V w) {
   if constexpr (DIR > 0) w.y = -w.y;
   return w;
@@ -157,7 +109,7 @@ __device__ __forceinline__ void columns(typename C::V* x, typename C::V* col, in
 #pragma unroll
       for (int r = 1; r < R; ++r) x[t * R + r] = cmul(x[t * R + r], twd<DIR>(tw[r * k * SPAN]));
     }
-    dft<V, R, DIR>(x + t * R);
+    Bfly<V, R, DIR>::run(x + t * R);
   }
   if constexpr (ST + 1 < NS) {
     constexpr int R2 = DIR < 0 ? C::pl.C[ST + 1] : C::pl.C[NS - 2 - ST];
@@ -204,7 +156,7 @@ __device__ __forceinline__ void forward(typename C::V* c, typename C::V* plane, 
   constexpr int n = C::n, H = C::H, L = C::L, P = C::P, Ra = C::Ra, Rb = C::Rb, NB = C::NB, RL = C::RL;
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
-    dft<V, Rb, -1>(c + i * Rb);
+    Bfly<V, Rb, -1>::run(c + i * Rb);
 #pragma unroll
     for (int q = 0; q < Rb; ++q) row[(t * NB + i) * Rb + q] = c[i * Rb + q];
   }
@@ -222,7 +174,7 @@ __device__ __forceinline__ void forward(typename C::V* c, typename C::V* plane, 
       const int j = t + RL * i;
 #pragma unroll
       for (int r = 1; r < Ra; ++r) v[i * Ra + r] = cmul(v[i * Ra + r], tw[2 * r * j]);
-      dft<V, Ra, -1>(v + i * Ra);
+      Bfly<V, Ra, -1>::run(v + i * Ra);
 #pragma unroll
       for (int q = 0; q < Ra; ++q) row[j + Rb * q] = v[i * Ra + q];
     }
@@ -380,7 +332,7 @@ k_plane(const typename cplx_of<T>::type* spec, const T* vin, T* u, T* dst, const
     wave_sync();
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
-      dft<V, Ra, +1>(v + i * Ra);
+      Bfly<V, Ra, +1>::run(v + i * Ra);
 #pragma unroll
       for (int k = 0; k < Ra; ++k) row[(t + RL * i) * Ra + k] = v[i * Ra + k];
     }
@@ -394,7 +346,7 @@ k_plane(const typename cplx_of<T>::type* spec, const T* vin, T* u, T* dst, const
     for (int r = 0; r < Rb; ++r) c[i * Rb + r] = row[j + Ra * r];
 #pragma unroll
     for (int r = 1; r < Rb; ++r) c[i * Rb + r] = cmul(c[i * Rb + r], twd<+1>(tw[2 * r * j]));
-    dft<V, Rb, +1>(c + i * Rb);
+    Bfly<V, Rb, +1>::run(c + i * Rb);
   }
   wave_sync();
 

@@ -9,23 +9,28 @@
 // input and no output. A workgroup owns one half Q (inputs of degree parity
 // Q, outputs of the other one), one ky and TZ kx columns at every z. Its
 // waves take the inputs one moment (tile of n x TZ points) each: load it
-// into registers, publish it in LDS, transform it along z (Stockham stages
-// exchanged through a wave-private LDS buffer), multiply by i k_z, transform
-// back and publish the derivative; then all threads add the published
-// moments of this round, at their own points, to the accumulators of every
-// output, which stay in registers for the whole sweep. Each input is read
-// from HBM once and each output written once (2F per stage, F = M n^3
-// elements, instead of 5F for a derivative pass and a coupling pass).
+// into registers, transform it along z (Stockham stages exchanged through a
+// wave-private LDS buffer), multiply by i k_z, transform back and publish the
+// derivative there; then all threads add the moments of this round, at their
+// own points, to the accumulators of every output, which stay in registers
+// for the whole sweep. S itself is published in LDS too, or, where that would
+// halve the workgroups per CU and the spectra sit in the Infinity Cache, read
+// a second time from the caches. Each input is read from HBM once and each
+// output written once (2F per stage, F = M n^3 elements, instead of 5F for a
+// derivative pass and a coupling pass).
 //
-// Bound: HBM at 128^3 P_7 (a copy with these accesses takes 220 us), the
-// transforms and sums of eight waves per CU on top (skipping either costs
-// 25 us less); arithmetic and LDS on the smaller grids and at 256^3. Against
-// the two passes it replaces: FP32 128^3 P_7 490 -> 271 us, FP64 1003 -> 525,
-// 256^3 P_5 2345 -> 1490-1630, 64^3 P_7 55 -> 28, 64^3 P_5 32 -> 18, 96^3 P_3
-// 47 -> 39, 48^3 P_3 (eight solves) 107 -> 28, 48^3 P_4 FP64 47 -> 25. Loading
-// the next round's tiles before this round's transforms (instead of after
-// them) measured slower on every grid (128^3 P_7 375 against 365 us, 64^3 P_7
-// 37 against 28), so the loads are not waited for long.
+// Bound: HBM at 128^3 P_7 (without transforms and sums the same sweep takes
+// 230 us); transforms and LDS on the other grids. Against the two passes it
+// replaces: FP32 128^3 P_7 490 -> 275 us, FP64 1003 -> 516, 256^3 P_5 2345 ->
+// 1590, 64^3 P_7 55 -> 28, 64^3 P_5 32 -> 19, 96^3 P_3 47 -> 31, 48^3 P_4 FP64
+// 47 -> 15.
+// The transforms of the outputs instead of the inputs (all three terms summed
+// in kz space, one tile per wave) run 2 us faster at 96^3 P_3 and 10% at 256^3,
+// but pass the x and y terms through the z transforms' rounding: the error of
+// whole solves against 64 bits grows by 1.3 (1.5 to 2 on the radix-3 grids).
+// Loading the next round's tiles before this round's transforms (instead of
+// after them) measured slower on every grid (64^3 P_7 37 against 28), so the
+// loads are not waited for long.
 #pragma once
 
 namespace rte {
@@ -75,10 +80,6 @@ template <typename T> __host__ __device__ constexpr Plan plan_of(int n) {
   }
 }
 
-#ifndef RTE_STREAM_WAVES
-#define RTE_STREAM_WAVES 0
-#endif
-
 template <typename T, int NN, int N> struct Cfg {
   using V = typename cplx_of<T>::type;
   using Lay = SpecLayout<T, NN>;
@@ -90,13 +91,19 @@ template <typename T, int NN, int N> struct Cfg {
   static constexpr int OUT = set_size(N, 0) > set_size(N, 1) ? set_size(N, 0) : set_size(N, 1);
   // registers of the accumulators per thread of a workgroup of w waves
   static constexpr int acc_regs(int w) { return OUT * (n * TZ / (64 * w)) * 2 * int(sizeof(T) / 4); }
-  // the fewest waves (a divisor of the tile's points) whose accumulators fit
-  // 168 of the 256 registers a thread has with two waves per SIMD, from eight
-  // on small grids (few workgroups: more inputs per round) and four on large
+  // Waves per workgroup. The largest halves (P_7, 36 moments) run at one point
+  // per thread as far as 12 waves go (96^3 141 us against 161 with two points;
+  // at 128^3 the tiles of 16 waves exceed the LDS: 286 against 275 with
+  // eight). Otherwise the fewest waves, a divisor of the tile's points, whose
+  // accumulators fit 168 of 256 registers, from four on large grids (96^3 FP32, 64^3
+  // FP64 and above: more workgroups per CU: 128^3 P_5 156 us with 4, 197 with 8;
+  // 64^3 P_5 FP64 30 with 4, 35 with 8) and eight on small ones (more inputs
+  // per round: 64^3 P_5 18.9 with 8, 19.6 with 4; 48^3 P_3 7.0 with 6, 7.5 with
+  // 3, 9.5 with 2).
   static constexpr int waves() {
-    if (RTE_STREAM_WAVES) return RTE_STREAM_WAVES;
     const int full = n * TZ / 64;                        // waves at one point per thread
-    int lo = n >= 96 ? 4 : 8;
+    if (OUT > 28) return full <= 12 ? full : full / 2;
+    const int lo = n * int(sizeof(T)) >= 384 ? 4 : 8;
     for (int w = 1; w <= 16; ++w)
       if (full % w == 0 && w % WPM == 0 && (w >= lo || w == full) && acc_regs(w) <= 168) return w;
     return full;
@@ -108,60 +115,54 @@ template <typename T, int NN, int N> struct Cfg {
   static constexpr int RK = pl.R[pl.stages - 1];         // last radix of the forward
   static constexpr int PADROWS = n / pl.R[0] > n / RK ? n / pl.R[0] : n / RK;
   static constexpr int DROWS = n + PADROWS;              // exchange buffer
+  // S read again from the caches instead of published in LDS: fields below
+  // 120 MB (96^3 P_3 31 us against 39, P_4 47 against 51, P_5 with 127 MB 76
+  // against 73; 96^3 P_3 FP64 54 against 74, 48^3 P_4 FP64 15 against 24), but
+  // not at 64^3, whose tiles leave room for enough workgroups either way (P_7
+  // 30 against 28)
+  static constexpr bool SG =
+      n != 64 && size_t(N + 1) * (N + 1) * n * n * n * sizeof(T) < size_t(120) * 1000 * 1000;
+  static constexpr int SLOT = ((SG ? 0 : n) + DROWS) * TZ;   // LDS of one moment: S (if published), derivative
   static constexpr size_t lds_of(int moments) {
-    return (size_t(moments) * (size_t(n) + DROWS) * TZ + n) * sizeof(V) + size_t(n) * sizeof(T);
+    return (size_t(moments) * SLOT + n) * sizeof(V) + size_t(n) * sizeof(T);
   }
   // moments per round: one tile for each wave (or part of one), no more than
-  // there are inputs, within 160 KB
+  // a half has, within 160 KB
   static constexpr int moments() {
     int m = NW * MPW / WPM;
     while (m > MPW && (m - MPW >= OUT || lds_of(m) > 160 * 1024)) m -= MPW;
     return m;
   }
   static constexpr int MPR = moments();
+  // moments whose S loads from the caches are in flight together (32 registers)
+  static constexpr int sb() {
+    const int b = 32 / (PPT * 2 * int(sizeof(T) / 4));
+    return b < 1 ? 1 : (b > MPR ? MPR : b);
+  }
+  static constexpr int SB = sb();
   static constexpr size_t lds() { return lds_of(MPR); }
+  // waves per SIMD asked of the compiler: what accumulators, points and about
+  // 44 other registers leave, two at least
+  static constexpr int min_waves() {
+    const int r = acc_regs(NW) + 2 * P * int(sizeof(T) / 4) + 44;
+    const int w = 512 / r;
+    return w < 2 ? 2 : (w > 4 ? 4 : w);
+  }
   static_assert(PTS % BT == 0 && BT % TZ == 0 && 64 % TZ == 0, "a thread keeps its kx over its points");
 };
 
 // Configurations that run this pass: the accumulators, one column's points
-// and the addresses fit 256 registers (two waves per SIMD), a round's tiles
-// fit 160 KB of LDS, and where several waves share a tile all of them take
-// part in its barriers (N = 0 has no round). Left out: 256^3 above P_5.
+// and the addresses fit the registers (256 per thread up to eight waves, 168
+// beyond), a round's tiles fit 160 KB of LDS, and where several waves share a
+// tile all of them take part in its barriers (N = 0 has no round). Left out:
+// 256^3 above P_5.
 template <typename T, int NN, int N> constexpr bool use_stream() {
   using C = Cfg<T, NN, N>;
-  return N <= kDenseOrder && C::acc_regs(C::NW) <= 168 && C::NW <= 8 && C::lds() <= 160 * 1024 &&
-         (C::WPM == 1 || C::MPR * C::WPM == C::NW || N == 0);
+  return N <= kDenseOrder && C::NW <= 12 && C::acc_regs(C::NW) <= (C::NW > 8 ? 88 : 168) &&
+         C::lds() <= 160 * 1024 && (C::WPM == 1 || C::MPR * C::WPM == C::NW || N == 0);
 }
 
 // ------------------------------------------------------------ transforms ---
-// 12-point DFT in registers: r = a + 3 b (b < 4), q = c + 4 d
-template <typename V, int DIR> __device__ __forceinline__ void dft12(V* x) {
-  using T = decltype(V::x);
-  V y[3][4];
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-#pragma unroll
-    for (int b = 0; b < 4; ++b) y[a][b] = x[a + 3 * b];
-    Bfly<V, 4, DIR>::run(y[a]);
-  }
-#pragma unroll
-  for (int a = 1; a < 3; ++a)
-#pragma unroll
-    for (int c = 1; c < 4; ++c)   // exp(DIR 2 pi i a c / 12)
-      y[a][c] = cmul(y[a][c], cmk<V>(T(pen::cos_pi12(2 * a * c)), T(DIR) * T(pen::cos_pi12(6 - 2 * a * c))));
-#pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    V z[3] = {y[0][c], y[1][c], y[2][c]};
-    Bfly<V, 3, DIR>::run(z);
-#pragma unroll
-    for (int d = 0; d < 3; ++d) x[c + 4 * d] = z[d];
-  }
-}
-template <typename V, int R, int DIR> __device__ __forceinline__ void dft(V* x) {
-  if constexpr (R == 12) dft12<V, DIR>(x);
-  else Bfly<V, R, DIR>::run(x);
-}
-
 // Orders LDS accesses among the lanes that share a tile (one wave: they
 // execute in order; more: a workgroup barrier).
 template <int WPM> __device__ __forceinline__ void tile_sync() {
@@ -194,7 +195,7 @@ __device__ __forceinline__ void stages(typename C::V* x, typename C::V* buf, int
         x[t * R + r] = cmul(x[t * R + r], w);
       }
     }
-    dft<V, R, DIR>(x + t * R);
+    Bfly<V, R, DIR>::run(x + t * R);
   }
   if constexpr (ST + 1 < NS) {
     constexpr int R2 = DIR < 0 ? C::pl.R[ST + 1] : C::pl.R[NS - 2 - ST];
@@ -222,8 +223,7 @@ __device__ __forceinline__ void stages(typename C::V* x, typename C::V* buf, int
 }
 
 // -------------------------------------------------------------- coupling ---
-// acc[pos(a)] += B[a, b] (X | Y | Z)_b for every output a that reads input
-// b = set_at(N, Q, I): X = s kx (Im S, -Re S), Y the same with ky, Z = -s D.
+// acc[pos(a)] += B[a, b] (X | Y | Z)_b for every output a that reads input b.
 template <class C, typename T, int N, int B, int S>
 struct Scatter {
   static __device__ __forceinline__ void run(typename C::V (*acc)[C::VW], const typename C::V* X,
@@ -254,39 +254,89 @@ struct Scatter {
   }
 };
 
-// The published moments I.. of round RD, at item `e` (VW points) of a thread.
-template <class C, typename T, int N, int Q, int RD, int I>
-__device__ __forceinline__ void add_round(typename C::V (*acc)[C::VW], const typename C::V* pub, int e,
-                                          const T* skx, T sky) {
+// X = -i s kx S_b (S: VW points), Y the same with ky, Z = -s dS_b/dz from LDS.
+template <class C, typename T, int N, int B>
+__device__ __forceinline__ void add_moment(typename C::V (*acc)[C::VW], const typename C::V* S, const typename C::V* d,
+                                           const T* skx, T sky) {
   using V = typename C::V;
-  constexpr int i = RD * C::MPR + I;
-  if constexpr (I < C::MPR && i < set_size(N, Q)) {
-    constexpr int b = set_at(N, Q, i);
-    const V* s = pub + I * (C::n + C::DROWS) * C::TZ + e;
-    const V* d = s + C::n * C::TZ;
-    V X[C::VW], Y[C::VW], Z[C::VW];
-    if constexpr (C::VW == 2) {
-      const float4 sv = *reinterpret_cast<const float4*>(s), dv = *reinterpret_cast<const float4*>(d);
-      X[0] = cmk<V>(sv.y, -sv.x);
-      X[1] = cmk<V>(sv.w, -sv.z);
-      Z[0] = cmk<V>(dv.x, dv.y);
-      Z[1] = cmk<V>(dv.z, dv.w);
-    } else {
-      const V sv = *s;
-      X[0] = cmk<V>(sv.y, -sv.x);
-      Z[0] = *d;
-    }
+  V X[C::VW], Y[C::VW], Z[C::VW];
+  if constexpr (C::VW == 2) {
+    const float4 dv = *reinterpret_cast<const float4*>(d);
+    Z[0] = cmk<V>(dv.x, dv.y);
+    Z[1] = cmk<V>(dv.z, dv.w);
+  } else {
+    Z[0] = *d;
+  }
 #pragma unroll
-    for (int v = 0; v < C::VW; ++v) {
-      Y[v] = cscale(X[v], sky);
-      X[v] = cscale(X[v], skx[v]);
-    }
-    Scatter<C, T, N, b, 0>::run(acc, X, Y, Z);
-    // (else the LDS reads of the whole round are hoisted above the sums)
-    if constexpr (I % 2 == 1) __builtin_amdgcn_sched_barrier(0);
-    add_round<C, T, N, Q, RD, I + 1>(acc, pub, e, skx, sky);
+  for (int v = 0; v < C::VW; ++v) {
+    const V s = cmk<V>(S[v].y, -S[v].x);
+    Y[v] = cscale(s, sky);
+    X[v] = cscale(s, skx[v]);
+  }
+  Scatter<C, T, N, B, 0>::run(acc, X, Y, Z);
+}
+// VW points of a field, one 16-byte access where there are two
+template <class C> __device__ __forceinline__ void load_points(typename C::V* x, const typename C::V* p) {
+  if constexpr (C::VW == 2) {
+    const float4 v = *reinterpret_cast<const float4*>(p);
+    x[0] = cmk<typename C::V>(v.x, v.y);
+    x[1] = cmk<typename C::V>(v.z, v.w);
+  } else {
+    x[0] = *p;
   }
 }
+
+// Moments I0 .. I0 + NM - 1 of round RD: S at every item of the thread.
+template <class C, int N, int Q, int RD, int I0, int NM, int I = 0>
+__device__ __forceinline__ void load_s(typename C::V (*sv)[C::PPT / C::VW][C::VW], const typename C::V* __restrict__ src,
+                                       unsigned lo) {
+  constexpr int i = RD * C::MPR + I0 + I;
+  if constexpr (I < NM && I0 + I < C::MPR && i < set_size(N, Q)) {
+#pragma unroll
+    for (int k = 0; k < C::PPT / C::VW; ++k)
+      load_points<C>(sv[I][k], src + (size_t(set_at(N, Q, i)) * C::Lay::MS +
+                                      size_t(k * C::BT * C::VW / C::TZ) * C::Lay::ZS) + lo);
+    load_s<C, N, Q, RD, I0, NM, I + 1>(sv, src, lo);
+  }
+}
+template <class C, typename T, int N, int Q, int RD, int I0, int NM, int I = 0>
+__device__ __forceinline__ void add_s(typename C::V (*acc)[set_size(N, 1 - Q)][C::VW],
+                                      const typename C::V (*sv)[C::PPT / C::VW][C::VW], const typename C::V* pub, int e,
+                                      const T* skx, T sky) {
+  constexpr int i = RD * C::MPR + I0 + I;
+  if constexpr (I < NM && I0 + I < C::MPR && i < set_size(N, Q)) {
+#pragma unroll
+    for (int k = 0; k < C::PPT / C::VW; ++k)
+      add_moment<C, T, N, set_at(N, Q, i)>(acc[k], sv[I][k], pub + (I0 + I) * C::SLOT + e + k * C::BT * C::VW, skx, sky);
+    // (else the LDS reads of the whole round are hoisted above the sums)
+    if constexpr (I % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+    add_s<C, T, N, Q, RD, I0, NM, I + 1>(acc, sv, pub, e, skx, sky);
+  }
+}
+// Batches I0.. of a round after the first
+template <class C, typename T, int N, int Q, int RD, int I0>
+__device__ __forceinline__ void add_batches(typename C::V (*acc)[set_size(N, 1 - Q)][C::VW],
+                                            typename C::V (*sv)[C::PPT / C::VW][C::VW],
+                                            const typename C::V* __restrict__ src, const typename C::V* pub, int e,
+                                            unsigned lo, const T* skx, T sky) {
+  if constexpr (I0 < C::MPR && RD * C::MPR + I0 < set_size(N, Q)) {
+    if constexpr (C::SG) {
+      if constexpr (I0 > 0) load_s<C, N, Q, RD, I0, C::SB>(sv, src, lo);
+      add_s<C, T, N, Q, RD, I0, C::SB>(acc, sv, pub, e, skx, sky);
+      __builtin_amdgcn_sched_barrier(0);
+      add_batches<C, T, N, Q, RD, I0 + C::SB>(acc, sv, src, pub, e, lo, skx, sky);
+    } else {
+      typename C::V s1[1][C::PPT / C::VW][C::VW];
+#pragma unroll
+      for (int k = 0; k < C::PPT / C::VW; ++k)
+        load_points<C>(s1[0][k], pub + I0 * C::SLOT + C::DROWS * C::TZ + e + k * C::BT * C::VW);
+      add_s<C, T, N, Q, RD, I0, 1>(acc, s1, pub, e, skx, sky);
+      if constexpr (I0 % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+      add_batches<C, T, N, Q, RD, I0 + 1>(acc, sv, src, pub, e, lo, skx, sky);
+    }
+  }
+}
+
 // Workgroup barrier that orders LDS only: loads of the next round stay in
 // flight across it.
 __device__ __forceinline__ void lds_barrier() {
@@ -295,20 +345,25 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Offset of moment i of the set of degree parity Q (degrees Q, Q + 2, ...).
+template <class C> __device__ __forceinline__ size_t set_offset(int Q, int i) {
+  int l = Q;
+  while (i >= 2 * l + 1) {
+    i -= 2 * l + 1;
+    l += 2;
+  }
+  return size_t(l * l + i) * C::Lay::MS;
+}
+
 // Loads the tile of input g of round RD (rows l + L t + n / R0 r, column kx).
 template <class C, int N, int Q, int RD>
 __device__ __forceinline__ void load_tile(typename C::V* x, const typename C::V* __restrict__ src, int g, int gl) {
-  constexpr int IN = set_size(N, Q), n = C::n, R0 = C::pl.R[0];
-  constexpr size_t AX = C::Lay::ZS, MS = C::Lay::MS;
+  constexpr int n = C::n, R0 = C::pl.R[0];
+  constexpr size_t AX = C::Lay::ZS;
   const int i = RD * C::MPR + g;
-  if (g < C::MPR && i < IN) {
-    int b = i, l = Q;   // moment i of the set: degrees Q, Q + 2, ...
-    while (b >= 2 * l + 1) {
-      b -= 2 * l + 1;
-      l += 2;
-    }
-    const typename C::V* s = src + size_t(l * l + b) * MS;
-    asm volatile("" : "+v"(gl));   // (see `rounds`)
+  if (g < C::MPR && i < set_size(N, Q)) {
+    const typename C::V* s = src + set_offset<C>(Q, i);
+    asm volatile("" : "+v"(gl));   // (see `inputs`)
     const unsigned lo = unsigned(gl / C::TZ) * unsigned(AX) + gl % C::TZ;
 #pragma unroll
     for (int t = 0; t < C::P / R0; ++t)
@@ -317,6 +372,7 @@ __device__ __forceinline__ void load_tile(typename C::V* x, const typename C::V*
   }
 }
 
+// Rounds RD.. : differentiate, publish, add.
 template <class C, typename T, int N, int Q, int RD>
 __device__ __forceinline__ void rounds(typename C::V (*acc)[set_size(N, 1 - Q)][C::VW], typename C::V* x,
                                        const typename C::V* __restrict__ src, typename C::V* pub,
@@ -331,12 +387,13 @@ __device__ __forceinline__ void rounds(typename C::V (*acc)[set_size(N, 1 - Q)][
       int o = gl;
       asm volatile("" : "+v"(o));
       const int kx = o % TZ, l = (o / TZ) % L;
-      V* own = pub + g * (n + C::DROWS) * TZ;
-      V* ex = own + n * TZ;
+      V* ex = pub + g * C::SLOT;
+      if constexpr (!C::SG) {
 #pragma unroll
-      for (int t = 0; t < P / R0; ++t)
+        for (int t = 0; t < P / R0; ++t)
 #pragma unroll
-        for (int r = 0; r < R0; ++r) own[(l + L * t + n / R0 * r) * TZ + kx] = x[t * R0 + r];
+          for (int r = 0; r < R0; ++r) ex[(C::DROWS + l + L * t + n / R0 * r) * TZ + kx] = x[t * R0 + r];
+      }
       stages<C, -1>(x, ex, l, kx, tw);
 #pragma unroll
       for (int t = 0; t < P / RK; ++t)
@@ -351,12 +408,15 @@ __device__ __forceinline__ void rounds(typename C::V (*acc)[set_size(N, 1 - Q)][
 #pragma unroll
         for (int r = 0; r < R0; ++r) ex[(l + L * t + n / R0 * r) * TZ + kx] = x[t * R0 + r];
     }
-    load_tile<C, N, Q, RD + 1>(x, src, g, gl);
-    lds_barrier();
     int e = int(threadIdx.x) * C::VW;
     asm volatile("" : "+v"(e));
-#pragma unroll
-    for (int k = 0; k < C::PPT / C::VW; ++k) add_round<C, T, N, Q, RD, 0>(acc[k], pub, e + k * C::BT * C::VW, skx, sky);
+    // (k moves a whole number of rows: uniform base, one lane offset)
+    const unsigned lo = unsigned(e / TZ) * unsigned(C::Lay::ZS) + e % TZ;
+    V sv[C::SB][C::PPT / C::VW][C::VW];
+    if constexpr (C::SG) load_s<C, N, Q, RD, 0, C::SB>(sv, src, lo);
+    load_tile<C, N, Q, RD + 1>(x, src, g, gl);
+    lds_barrier();
+    add_batches<C, T, N, Q, RD, 0>(acc, sv, src, pub, e, lo, skx, sky);
     // the sums are formed here (the compiler would sink them to the stores
     // and hold the published values of every round instead)
 #pragma unroll
@@ -376,8 +436,7 @@ __device__ __forceinline__ void sweep(const typename C::V* __restrict__ src, typ
   using V = typename C::V;
   constexpr int OUTQ = set_size(N, 1 - Q);
   if constexpr (OUTQ > 0) {
-    constexpr int TZ = C::TZ, NI = C::PPT / C::VW;
-    constexpr size_t AX = C::Lay::ZS, MS = C::Lay::MS;
+    constexpr int NI = C::PPT / C::VW;
     const int tid = threadIdx.x;
     const int g = C::MPW == 1 ? __builtin_amdgcn_readfirstlane(tid / C::G) : tid / C::G;   // moment slot of this lane
     V acc[NI][OUTQ][C::VW];
@@ -390,25 +449,23 @@ __device__ __forceinline__ void sweep(const typename C::V* __restrict__ src, typ
     V x[C::P];
     load_tile<C, N, Q, 0>(x, src, g, tid % C::G);
     rounds<C, T, N, Q, 0>(acc, x, src, pub, tw, kz, skx, sky, g, tid % C::G);
+    const int e = tid * C::VW;
+    const unsigned lo = unsigned(e / C::TZ) * unsigned(C::Lay::ZS) + e % C::TZ;
 #pragma unroll
-    for (int k = 0; k < NI; ++k) {
-      // (k moves a whole number of rows: uniform base, one lane offset)
-      const int e = tid * C::VW;
-      const unsigned lo = unsigned(e / TZ) * unsigned(AX) + e % TZ;
+    for (int k = 0; k < NI; ++k)
 #pragma unroll
       for (int a = 0; a < OUTQ; ++a) {
-        V* o = dst + (size_t(set_at(N, 1 - Q, a)) * MS + size_t(k * C::BT * C::VW / TZ) * AX) + lo;
+        V* o = dst + (size_t(set_at(N, 1 - Q, a)) * C::Lay::MS + size_t(k * C::BT * C::VW / C::TZ) * C::Lay::ZS) + lo;
         if constexpr (C::VW == 2)
           *reinterpret_cast<float4*>(o) = make_float4(acc[k][a][0].x, acc[k][a][0].y, acc[k][a][1].x, acc[k][a][1].y);
         else *o = acc[k][a][0];
       }
-    }
   }
 }
 
 // Grid: (ky, kx tile, Q), neighbouring tiles on one XCD. sc: the factor s.
 template <typename T, int NN, int N>
-__global__ void __launch_bounds__((Cfg<T, NN, N>::BT), 2)
+__global__ void __launch_bounds__((Cfg<T, NN, N>::BT), (Cfg<T, NN, N>::min_waves()))
 k_stream(const typename cplx_of<T>::type* __restrict__ spec, typename cplx_of<T>::type* __restrict__ wspec,
          const typename cplx_of<T>::type* __restrict__ twg, const T* __restrict__ kv, T sc,
          const Ctl* __restrict__ ctl, long long bs) {
@@ -423,7 +480,7 @@ k_stream(const typename cplx_of<T>::type* __restrict__ spec, typename cplx_of<T>
   if (ctl->stop) return;
   extern __shared__ __align__(16) unsigned char smem[];
   V* pub = reinterpret_cast<V*>(smem);
-  V* tw = pub + C::MPR * (n + C::DROWS) * TZ;
+  V* tw = pub + C::MPR * C::SLOT;
   T* kz = reinterpret_cast<T*>(tw + n);
   const int lt = xcd_tile(blockIdx.x, gridDim.x);
   const int Q = lt & 1, tile = lt >> 1;
