@@ -71,12 +71,6 @@ bool coupling_dense(int N, std::vector<double>& bx, std::vector<double>& by,
 // (D (k.B) D^T = (X k).B); false if the check fails or N is out of range.
 bool rotation_x90(int N, std::vector<double>& D);
 
-// Coupling slot table of the high-order pass: per row a, the non-zeros of
-// the real-basis streaming matrices as codes (b << 2 | axis) in slot order,
-// -1 after the last, and their FP64 values. Returns false for an order that
-// is not built.
-bool coupling_table(int N, std::vector<int>& code, std::vector<double>& val);
-
 // Twiddles exp(-2 pi i t / n), t in [0, n), as interleaved (cos, sin) FP64.
 void twiddles(int n, std::vector<double>& tw);
 
@@ -154,9 +148,6 @@ struct StepArgs {
                             // the real kx = 0 and kx = n/2 columns)
   void* dspec;              // its z derivative, same layout
   void* wspec;              // coupled spectrum (orders above kDenseOrder only)
-  const int* ctab;          // coupling slots [M][kMaxSlots]: (b << 2 | axis), -1 ends
-                            // (orders above kDenseOrder only)
-  const void* cval;         // their coefficients [M][kMaxSlots] (working precision)
   const void* tw;           // twiddles exp(-2 pi i t / n), n complex
   const void* kv;           // wavenumbers, n
   const void* sig;          // per-degree loss [N+1][n^3]

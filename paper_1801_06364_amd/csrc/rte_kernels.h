@@ -16,8 +16,8 @@
 //   D  k_pencil     per (moment, ky, 16 kx columns): z FFT, times i k_z,
 //                   inverse z FFT -> D;
 //   C  k_couple     per spectral point, all moments in registers: W, written
-//                   over D (k_couple_rt for P_21: a run-time slot table, W to
-//                   a separate buffer);
+//                   over D (k_couple_high for P_21: the rows in four classes,
+//                   W to a separate buffer);
 //   P  k_plane      per (moment, z-plane): inverse y FFT, complex-to-real x
 //                   FFT and the fused pointwise epilogue (loss, in-scatter,
 //                   boundary layer, source, RK combine; after the last stage
@@ -444,66 +444,105 @@ k_couple(const typename cplx_of<T>::type* __restrict__ spec, typename cplx_of<T>
   }
 }
 
-// High orders (more moments than registers hold): one thread per spectral
-// point and row slice (blockIdx.y: the order groups |m| = g, g + kRtSlices,
-// ..., so that the small grids of high orders still give every SIMD several
-// wavefronts) walks its rows with the slot table, reading each input from
-// the spectrum (neighbouring shells stay in the caches across rows) and
-// writing W to a separate buffer, since later rows still need the inputs. All kMaxSlots
-// loads of a row are issued before any is used (a padding slot, code -1,
-// re-reads the row's first input and adds nothing), so a row costs one
-// memory latency instead of one per input. Rows go by order group, degree
-// ascending, (l, g) then (l, -g): their inputs are the degrees l +- 1 at
-// orders g and g +- 1, so rows l and l + 2 of a group share half of them
-// while they are still in L2 (and (l, +-g) share them in L1).
-constexpr int kRtSlices = 4;
+// High orders (P_21): rows of degree l read degrees l +- 1 only, and rows of
+// even |m| read S at odd |m| and D at even |m| (above), so the rows split into
+// four classes by the parities of l and |m| that share no input and no
+// output. One thread per spectral point and class (uniform per wavefront)
+// walks its rows by degree with the inputs of the two neighbouring degrees in
+// registers (at most 2 (2N + 1) values) and the next pair's loads issued one
+// row shell ahead. W goes to a separate buffer (another class reads the D
+// entries in its place). Bound: HBM, every input read once and every output
+// written once (3F): 64^3 P_21 FP32 289 us for 1.52 GB (5.3 TB/s; 172
+// registers). A pass that gathered each row's inputs by a table, nine reads
+// of every input from beyond L1, took 630 us.
+template <typename V, int N, int LP, int MP, int B, int END>
+struct LoadShellH {
+  static __device__ __forceinline__ void run(V* x, const V* __restrict__ sp, const V* __restrict__ dp, size_t ms) {
+    if constexpr (B < END) {
+      x[B - isqrt_c(B) * isqrt_c(B)] = (m_parity(B) != MP ? sp : dp)[B * ms];
+      LoadShellH<V, N, LP, MP, B + 1, END>::run(x, sp, dp, ms);
+    }
+  }
+};
+// Row A of shell l: lo, hi: the inputs of degrees l - 1 and l + 1 (indexed by
+// order + degree), S where the order's parity differs from the row's, else D.
+template <typename V, typename T, int N, int A, int S>
+struct RowAccH {
+  static __device__ __forceinline__ void run(const V* lo, const V* hi, T* acc) {
+    constexpr int l = isqrt_c(A), m = A - l * l - l;
+    constexpr SlotList sl = slots_of(N, l, m);
+    if constexpr (S < sl.count) {
+      constexpr int b = sl.b[S], lb = isqrt_c(b);
+      constexpr double c0 = ct::real_coef(N, 0, A, b), c1 = ct::real_coef(N, 1, A, b), c2 = ct::real_coef(N, 2, A, b);
+      static_assert((c0 == 0.0 && c1 == 0.0) || m_parity(b) != m_parity(A), "x, y coupling across |m| parities");
+      static_assert(c2 == 0.0 || m_parity(b) == m_parity(A), "z coupling within one |m| parity");
+      const V x = (lb < l ? lo : hi)[b - lb * lb];
+      if constexpr (c0 != 0.0) {
+        acc[0] += T(c0) * x.x;
+        acc[1] += T(c0) * x.y;
+      }
+      if constexpr (c1 != 0.0) {
+        acc[2] += T(c1) * x.x;
+        acc[3] += T(c1) * x.y;
+      }
+      if constexpr (c2 != 0.0) {
+        acc[4] += T(c2) * x.x;
+        acc[5] += T(c2) * x.y;
+      }
+      RowAccH<V, T, N, A, S + 1>::run(lo, hi, acc);
+    }
+  }
+};
+template <typename V, typename T, int N, int MP, int A, int END>
+struct RowsH {
+  static __device__ __forceinline__ void run(const V* lo, const V* hi, V* __restrict__ out, size_t ms, T kx, T ky, T sc) {
+    if constexpr (A < END) {
+      if constexpr (m_parity(A) == MP) {
+        T acc[6] = {0, 0, 0, 0, 0, 0};
+        RowAccH<V, T, N, A, 0>::run(lo, hi, acc);
+        const T re = kx * acc[0] + ky * acc[2], im = kx * acc[1] + ky * acc[3];
+        // -i (re + i im) - (dre + i dim)
+        out[A * ms] = cmk<V>(sc * (im - acc[4]), sc * (-re - acc[5]));
+      }
+      RowsH<V, T, N, MP, A + 1, END>::run(lo, hi, out, ms, kx, ky, sc);
+    }
+  }
+};
+// Shells l = L, L + 2, ..: lo holds degree L - 1, hi receives degree L + 1.
+template <typename V, typename T, int N, int MP, int L>
+__device__ __forceinline__ void shells_h(V* lo, V* hi, const V* __restrict__ sp, const V* __restrict__ dp,
+                                         V* __restrict__ out, size_t ms, T kx, T ky, T sc) {
+  if constexpr (L <= N) {
+    if constexpr (L + 1 <= N) LoadShellH<V, N, L & 1, MP, (L + 1) * (L + 1), (L + 2) * (L + 2)>::run(hi, sp, dp, ms);
+    RowsH<V, T, N, MP, L * L, (L + 1) * (L + 1)>::run(lo, hi, out, ms, kx, ky, sc);
+    shells_h<V, T, N, MP, L + 2>(hi, lo, sp, dp, out, ms, kx, ky, sc);
+  }
+}
 
-template <typename T, int NN>
+template <typename T, int NN, int N>
 __global__ void __launch_bounds__(kCBlock)
-k_couple_rt(const typename cplx_of<T>::type* __restrict__ spec,
-            const typename cplx_of<T>::type* __restrict__ dspec, typename cplx_of<T>::type* __restrict__ out,
-            const T* __restrict__ kv, const int* __restrict__ code, const T* __restrict__ val, int M, T sc,
-            const Ctl* __restrict__ ctl) {
+k_couple_high(const typename cplx_of<T>::type* __restrict__ spec, const typename cplx_of<T>::type* __restrict__ dspec,
+              typename cplx_of<T>::type* __restrict__ out, const T* __restrict__ kv, T sc, const Ctl* __restrict__ ctl) {
   using V = typename cplx_of<T>::type;
   constexpr int n = NN, H = NN / 2;
-  constexpr size_t MS = size_t(n) * n * H;
+  constexpr size_t MS = SpecLayout<T, NN>::MS;
   if (ctl->stop) return;
-  const int pt = blockIdx.x * kCBlock + threadIdx.x;
+  const int cls = blockIdx.x & 3;
+  const int pt = (blockIdx.x >> 2) * kCBlock + threadIdx.x;
   if (pt >= n * n * H) return;
-  const int N = isqrt_c(M - 1);
   const T kx = kv[pt % H], ky = kv[SpecLayout<T, NN>::ky_of(pt)];
-  for (int g = int(blockIdx.y); g <= N; g += kRtSlices)
-  for (int l = g; l <= N; ++l)
-  for (int sg = 0; sg < (g > 0 ? 2 : 1); ++sg) {
-    const int a = l * l + l + (sg ? -g : g);
-    const int* cr = code + size_t(a) * kMaxSlots;
-    const T* vr = val + size_t(a) * kMaxSlots;
-    const int c0 = max(cr[0], 0);   // (moment 0, x) if a row had no slot
-    V x[kMaxSlots];
-    int ax[kMaxSlots];
-    T w[kMaxSlots];
-#pragma unroll
-    for (int k = 0; k < kMaxSlots; ++k) {
-      const int c = cr[k];
-      const int cc = c >= 0 ? c : c0;
-      ax[k] = c >= 0 ? (c & 3) : 3;
-      w[k] = vr[k];
-      x[k] = ((cc & 3) == 2 ? dspec : spec)[size_t(cc >> 2) * MS + pt];
-    }
-    // per-axis weights by selects (no branches, so the weight loads stay
-    // ahead of the input loads)
-    T acc[6] = {0, 0, 0, 0, 0, 0};
-#pragma unroll
-    for (int k = 0; k < kMaxSlots; ++k) {
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        const T wd = ax[k] == d ? w[k] : T(0);
-        acc[2 * d] += wd * x[k].x;
-        acc[2 * d + 1] += wd * x[k].y;
-      }
-    }
-    const T re = kx * acc[0] + ky * acc[2], im = kx * acc[1] + ky * acc[3];
-    out[size_t(a) * MS + pt] = cmk<V>(sc * (im - acc[4]), sc * (-re - acc[5]));
+  const V* sp = spec + pt;
+  const V* dp = dspec + pt;
+  V a[2 * N + 1], b[2 * N + 1];
+  // even l: shell 0 has no lower neighbour; odd l: shell 1 reads degree 0
+  if (cls == 0) shells_h<V, T, N, 0, 0>(a, b, sp, dp, out + pt, MS, kx, ky, sc);
+  else if (cls == 1) shells_h<V, T, N, 1, 0>(a, b, sp, dp, out + pt, MS, kx, ky, sc);
+  else if (cls == 2) {
+    LoadShellH<V, N, 1, 0, 0, 1>::run(a, sp, dp, MS);
+    shells_h<V, T, N, 0, 1>(a, b, sp, dp, out + pt, MS, kx, ky, sc);
+  } else {
+    LoadShellH<V, N, 1, 1, 0, 1>::run(a, sp, dp, MS);
+    shells_h<V, T, N, 1, 1>(a, b, sp, dp, out + pt, MS, kx, ky, sc);
   }
 }
 
@@ -1792,8 +1831,8 @@ void enqueue_stage(const StepArgs& a, ProfRec* pr, double hs, double sgn, const 
                          T(sgn * hs / n2), cctl, bs);
     } else {
       coupled = static_cast<V*>(a.wspec);
-      hipLaunchKernelGGL((k_couple_rt<T, NN>), dim3(cblocks, kRtSlices), cblk, 0, st, spec, dspec, coupled, kv, a.ctab,
-                         static_cast<const T*>(a.cval), M, T(sgn * hs / n2), cctl);
+      hipLaunchKernelGGL((k_couple_high<T, NN, N>), dim3(4 * cblocks), cblk, 0, st, spec, dspec, coupled, kv,
+                         T(sgn * hs / n2), cctl);
     }
   }
   rec(PROF_COUPLE);

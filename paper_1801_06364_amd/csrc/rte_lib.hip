@@ -66,7 +66,7 @@ constexpr size_t kAlign = 256;
 inline size_t up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
-  size_t u, v, spec, dspec, wspec, ctab, cval, sig, q, qflag, tw, kv, det, readings, resid, partial, phi_int,
+  size_t u, v, spec, dspec, wspec, sig, q, qflag, tw, kv, det, readings, resid, partial, phi_int,
       gin, ctl,
       total;
 };
@@ -101,11 +101,9 @@ inline Layout layout_of(const rte_config* c, bool has_q) {
   L.v = o; o = up(o + M * V * s);
   L.spec = o; o = up(o + M * n * n * (n / 2) * 2 * s);
   L.dspec = o; o = up(o + M * n * n * (n / 2) * 2 * s);
-  // orders above kDenseOrder: coupled-spectrum buffer and slot table
+  // orders above kDenseOrder: coupled-spectrum buffer
   const bool high = c->order_N > kDenseOrder;
   L.wspec = o; o = up(o + (high ? M * n * n * (n / 2) * 2 * s : 0));
-  L.ctab = o; o = up(o + (high ? M * kMaxSlots * sizeof(int) : 0));
-  L.cval = o; o = up(o + (high ? M * kMaxSlots * s : 0));
   L.sig = o; o = up(o + size_t(c->order_N + 1) * V * s);
   L.q = o; o = up(o + (has_q ? M * V * s : 0));
   L.qflag = o; o = up(o + n * sizeof(int));
@@ -359,14 +357,6 @@ int upload_tables_t(rte_handle* h, const rte_medium* med, const std::vector<doub
     put(L.gin, gin.data(), V * 8);
   }
   if (h->cfg.n_det > 0) put(L.det, h->cfg.det_index, size_t(h->cfg.n_det) * 8);
-  if (h->N > kDenseOrder) {
-    std::vector<int> code;
-    std::vector<double> val;
-    if (!coupling_table(h->N, code, val)) return RTE_EINVAL;
-    put(L.ctab, code.data(), code.size() * sizeof(int));
-    convert_upload(tmp, val.data(), val.size());
-    put(L.cval, tmp.data(), tmp.size() * sizeof(T));
-  }
   return to_code(e);
 }
 
@@ -532,8 +522,6 @@ int create_impl(const rte_config* cfg, const rte_medium* med, void* dev_ws, size
   A.spec = h->ws + L.spec;
   A.dspec = h->ws + L.dspec;
   A.wspec = N > kDenseOrder ? h->ws + L.wspec : nullptr;
-  A.ctab = N > kDenseOrder ? h->at<int>(L.ctab) : nullptr;
-  A.cval = N > kDenseOrder ? h->ws + L.cval : nullptr;
   A.tw = h->ws + L.tw;
   A.kv = h->ws + L.kv;
   A.sig = h->ws + L.sig;

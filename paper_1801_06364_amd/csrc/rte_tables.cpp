@@ -252,30 +252,6 @@ bool rotation_x90(int N, std::vector<double>& D) {
   return true;
 }
 
-bool coupling_table(int N, std::vector<int>& code, std::vector<double>& val) {
-  std::vector<double> b[3];
-  if (!coupling_dense(N, b[0], b[1], b[2])) return false;
-  const int M = (N + 1) * (N + 1);
-  code.assign(size_t(M) * kMaxSlots, -1);
-  val.assign(size_t(M) * kMaxSlots, 0.0);
-  for (int l = 0; l <= N; ++l)
-    for (int m = -l; m <= l; ++m) {
-      const int a = idx(l, m);
-      const SlotList sl = slots_of(N, l, m);
-      int k = 0;
-      for (int s = 0; s < sl.count; ++s)
-        for (int ax = 0; ax < 3; ++ax) {
-          const double v = b[ax][size_t(a) * M + sl.b[s]];
-          if (v == 0.0) continue;
-          if (k == kMaxSlots) return false;
-          code[size_t(a) * kMaxSlots + k] = (sl.b[s] << 2) | ax;
-          val[size_t(a) * kMaxSlots + k] = v;
-          ++k;
-        }
-    }
-  return true;
-}
-
 void twiddles(int n, std::vector<double>& tw) {
   tw.assign(2 * size_t(n), 0.0);
   for (int t = 0; t < n; ++t) {

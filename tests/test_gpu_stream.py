@@ -15,7 +15,9 @@ log2(n^3) stages each way and at most 10 products per row accumulate rounding
 like sqrt(2 * 3 * log2(n) + 10) units in the last place, below 8 for n = 256;
 ten times that is 80 * 2^-24 = 5e-6 in FP32 and 80 * 2^-53 = 1e-14 in FP64.
 The step is read back as u + dt c S u with |dt c S u| >= 0.1 |u|, which adds
-one rounding of u: ten more units.
+one rounding of u: ten more units. P_21 (coupling by four classes of rows, z
+derivative in a pass of its own) in FP64: the reference's coefficients come from
+a quadrature that is within 7e-15 of the closed forms; 1e-14 more.
 """
 import numpy as np
 import pytest
@@ -29,8 +31,8 @@ TOL = {"f32": 6e-6, "f64": 1.2e-14}
 
 CASES = [
     # (n, orders)
-    (16, (0, 1, 2, 3, 4, 5, 6, 7)),
-    (32, (1, 4, 7)),
+    (16, (0, 1, 2, 3, 4, 5, 6, 7, 21)),
+    (32, (1, 4, 7, 21)),
     (48, (1, 3, 6, 7)),
     (64, (2, 5, 7)),
     (96, (1, 3, 6)),
@@ -81,10 +83,11 @@ def test_streaming_term_of_random_state(n, N, prec):
         ref = _long_double_term(n, N, dx, c, dt, psi)
     else:
         ref = pn.solve(n, N, dx, c, dt, zero, zero, zero, psi, None, 0, 0.01, 1.0, 1, scheme="euler")["state"] - psi
+    tol = TOL[prec] + (1e-14 if N == 21 and prec == "f64" else 0.0)
     assert np.linalg.norm(ref) >= 0.1 * np.linalg.norm(psi)
-    assert np.linalg.norm(got - ref) <= TOL[prec] * np.linalg.norm(ref)
+    assert np.linalg.norm(got - ref) <= tol * np.linalg.norm(ref)
     for a in range(M):
-        assert np.linalg.norm(got[a] - ref[a]) <= 2 * TOL[prec] * np.linalg.norm(ref) / np.sqrt(M), a
+        assert np.linalg.norm(got[a] - ref[a]) <= 2 * tol * np.linalg.norm(ref) / np.sqrt(M), a
 
 
 def test_streaming_term_256_p5_against_torch():
