@@ -152,7 +152,7 @@ struct StepArgs {
   const void* kv;           // wavenumbers, n
   const void* sig;          // per-degree loss [N+1][n^3]
   const void* q;            // source [M][n^3] or nullptr
-  const int* qflag;         // per z-plane: source present
+  const int* qflag;         // [M][n], per moment and z-plane: source present
   double* phi_int;          // integrated fluence [n^3]
   double* partial;          // per z-plane fluence-change partial sums [n][2]
   double* readings;         // [cap][ndet]
@@ -215,7 +215,7 @@ struct OpArgs {
   double coef;       // OP_ADJ_STAGE / OP_ADJ_GRAD: RK stage coefficient
   void* u;           // base state / accumulator
   const void* x;     // stage input
-  void* y;           // stage output
+  void* y;           // stage output; OP_STEP: the new state (null: over u)
   const double* gin; // g inside the real domain, > 1 in the layer
   double* gmua;      // gradient accumulators (FP64, n^3)
   double* gmus;

@@ -724,7 +724,7 @@ k_rows_inv(const typename cplx_of<T>::type* spec, const T* vin, T* u, T* dst,
   fft_batch<V, H, 2 * H, +1, RB, kZBlock>(tw, Lay::xat(pl));
   __syncthreads();
   double acc_d = 0.0, acc_o = 0.0;
-  const bool hasq = (q != nullptr) && qflag[z];
+  const bool hasq = (q != nullptr) && qflag[b * n + z];
   const T qs = hasq ? T(source_weight(ctl, stage, step1)) : T(0);
   epilogue<V, T, NN, RB, Lay, kZBlock, MODE, FUSE>(pl, y0, b, z, vin, u, dst, sig, q, hasq, qs, phi_int, h, dt,
                                                   acc_d, acc_o);
@@ -1960,6 +1960,7 @@ hipError_t enqueue_t(const StepArgs& a, const OpArgs& op, ProfRec* pr) {
     case OP_STEP: {
       T* u = static_cast<T*>(a.u);
       T* v = static_cast<T*>(a.v);
+      T* un = op.y ? static_cast<T*>(op.y) : u;
       if (pr) {
         (void)hipEventRecord(static_cast<hipEvent_t>(pr->ev0), st);
         pr->count = 0;
@@ -1971,15 +1972,15 @@ hipError_t enqueue_t(const StepArgs& a, const OpArgs& op, ProfRec* pr) {
       const bool have = op.fused != 0;
       if (a.scheme == 1) {
         // forward Euler (eq. 11 with the sign reading): u <- u + dt f(u)
-        enqueue_stage<T, NN, N, EPI_EULER, true>(a, pr, hc, 1.0, u, u, u, have, 0, s1);
+        enqueue_stage<T, NN, N, EPI_EULER, true>(a, pr, hc, 1.0, u, u, un, have, 0, s1);
       } else {
         enqueue_stage<T, NN, N, EPI_FIRST, true>(a, pr, kRkAlpha[0] * hc, 1.0, u, u, v, have, 0, s1);
         enqueue_stage<T, NN, N, EPI_MID, true>(a, pr, kRkAlpha[1] * hc, 1.0, v, u, v, true, 1, s1);
         enqueue_stage<T, NN, N, EPI_MID, true>(a, pr, kRkAlpha[2] * hc, 1.0, v, u, v, true, 2, s1);
-        enqueue_stage<T, NN, N, EPI_LAST, true>(a, pr, kRkAlpha[3] * hc, 1.0, v, u, u, true, 3, s1);
+        enqueue_stage<T, NN, N, EPI_LAST, true>(a, pr, kRkAlpha[3] * hc, 1.0, v, u, un, true, 3, s1);
       }
       const unsigned ns = a.nslot > 1 ? unsigned(a.nslot) : 1u;
-      hipLaunchKernelGGL((k_end_step<T>), dim3(1, ns), dim3(kBlock), 0, st, u, a.det, a.ndet, a.readings, a.resid,
+      hipLaunchKernelGGL((k_end_step<T>), dim3(1, ns), dim3(kBlock), 0, st, un, a.det, a.ndet, a.readings, a.resid,
                          a.cap, a.partial, partial_count<NN>(), static_cast<Ctl*>(a.ctl),
                          ns > 1 ? a.sstride : 0LL);
       if (pr && pr->count < kMaxProfLaunches) {

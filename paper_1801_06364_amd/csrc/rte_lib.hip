@@ -106,7 +106,7 @@ inline Layout layout_of(const rte_config* c, bool has_q) {
   L.wspec = o; o = up(o + (high ? M * n * n * (n / 2) * 2 * s : 0));
   L.sig = o; o = up(o + size_t(c->order_N + 1) * V * s);
   L.q = o; o = up(o + (has_q ? M * V * s : 0));
-  L.qflag = o; o = up(o + n * sizeof(int));
+  L.qflag = o; o = up(o + M * n * sizeof(int));
   L.tw = o; o = up(o + n * 2 * s);
   L.kv = o; o = up(o + n * s);
   L.det = o; o = up(o + size_t(c->n_det) * 8);
@@ -333,7 +333,7 @@ int upload_tables_t(rte_handle* h, const rte_medium* med, const std::vector<doub
   wavenumbers(n, h->cfg.dx_mm, kv);
   convert_upload(tmp, kv.data(), kv.size());
   put(L.kv, tmp.data(), tmp.size() * sizeof(T));
-  std::vector<int> qflag(n, 0);
+  std::vector<int> qflag(size_t(h->M) * n, 0);
   if (h->has_q && !med->q) {
     // a batch slot keeps the source section of the common layout: cleared
     if (e == hipSuccess) e = hipMemsetAsync(h->ws + L.q, 0, size_t(h->M) * V * sizeof(T), h->stream);
@@ -343,7 +343,7 @@ int upload_tables_t(rte_handle* h, const rte_medium* med, const std::vector<doub
       for (size_t i = 0; i < V; ++i) {
         const double val = (inside[i] && a < h->q_moments) ? med->q[size_t(a) * V + i] : 0.0;
         qm[size_t(a) * V + i] = val;
-        if (val != 0.0) qflag[i / (size_t(n) * n)] = 1;
+        if (val != 0.0) qflag[size_t(a) * n + i / (size_t(n) * n)] = 1;
       }
     convert_upload(tmp, qm.data(), qm.size());
     put(L.q, tmp.data(), tmp.size() * sizeof(T));
@@ -1021,12 +1021,12 @@ int adjoint_run(rte_handle* h, int64_t steps, int64_t every, void* adj_ws, size_
     ok(hipMemcpyAsync(seg, w + A.ckpt + size_t(j) * F, F, hipMemcpyDeviceToDevice, st));
     for (int64_t nn = n0; nn + 1 < n1; ++nn) {
       unsigned char* next = seg + size_t(nn - n0 + 1) * F;
-      ok(hipMemcpyAsync(next, seg + size_t(nn - n0) * F, F, hipMemcpyDeviceToDevice, st));
       StepArgs S = R;
-      S.u = next;
+      S.u = seg + size_t(nn - n0) * F;
       OpArgs o{};
       o.kind = OP_STEP;
-      o.fused = nn > n0;   // the copy has the spectrum that the step before left
+      o.y = next;
+      o.fused = nn > n0;   // the step before left the spectrum of its result
       o.step1 = s0 + nn + 1;
       op(S, o);
     }

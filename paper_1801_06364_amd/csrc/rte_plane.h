@@ -362,7 +362,7 @@ k_plane(const typename cplx_of<T>::type* spec, const T* vin, T* u, T* dst, const
     acc_d[p] = acc_o[p] = 0.0;
     plane_of(p, pb[p], pz[p]);
     psig[p] = isqrt_c(pb[p]) * n * n * n;
-    phq[p] = kSrc && (q != nullptr) && qflag[pz[p]];
+    phq[p] = kSrc && (q != nullptr) && qflag[pb[p] * n + pz[p]];
     pq[p] = phq[p] ? T(source_weight(ctl, stage, step1)) : T(0);
   }
   auto of = [](const auto* v, int p) { return C::PPW == 1 || p == 0 ? v[0] : v[C::PPW - 1]; };

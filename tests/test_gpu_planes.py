@@ -74,7 +74,9 @@ def test_growth_threshold_of_a_device_state(n, N, prec):
     limits = []
     s.set_state(psi)
     limits.append(struct.unpack_from("d", s.snapshot(), 32)[0])
-    s.set_state_device(torch.from_numpy(psi.ravel()).cuda())
+    dev = torch.from_numpy(psi.ravel()).cuda()
+    torch.cuda.synchronize()   # the solver runs on a stream of its own
+    s.set_state_device(dev)
     limits.append(struct.unpack_from("d", s.snapshot(), 32)[0])
     s.close()
     w = np.repeat(2 * np.arange(N + 1) + 1, 2 * np.arange(N + 1) + 1)

@@ -104,6 +104,7 @@ def test_streaming_term_256_p5_against_torch():
     s = Solver(n, N, dx, c, dt, zero, zero, zero, precision="f32", scheme="euler", stream=torch.cuda.Stream())
     g = torch.Generator(device="cuda").manual_seed(5)
     psi = torch.randn(M, n, n, n, generator=g, device="cuda", dtype=torch.float32).double()
+    torch.cuda.synchronize()   # the solver runs on a stream of its own
     s.set_state_device(psi.view(-1))
     s.step(1)
     torch.cuda.synchronize()
