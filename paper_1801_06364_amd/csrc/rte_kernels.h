@@ -1286,8 +1286,8 @@ k_expo(typename cplx_of<T>::type* __restrict__ spec, const typename cplx_of<T>::
 // only, i.e. on the integer f^2 = fx^2 + fy^2 + fz^2 of the grid frequencies:
 // k_expo_table builds, for every f^2 and m, E_m = exp(T M_z) and
 // Phi_m = int_0^T exp(s M_z) ds c (whole blocks, by scaling and squaring),
-// k_expo_frame rotates each point's moments and source to the k = z frame
-// and back, and k_expo_blocks applies the blocks in that frame. D(R) = X^T Rz(-theta) X Rz(-phi): Rz rotates the (m, -m)
+// k_expo_rotated takes each point's moments and source to the k = z frame,
+// applies the blocks there and rotates back. D(R) = X^T Rz(-theta) X Rz(-phi): Rz rotates the (m, -m)
 // pairs by m times the angle, X (rotation by 90 degrees about x, y -> z) is
 // a constant per-degree matrix computed once on the host.
 
@@ -1419,7 +1419,17 @@ __device__ __forceinline__ void shell_rot_z(V* v, const T* cm, const T* sm) {
   }
 }
 
-// v <- X_L v (TRANS: X_L^T v), the degree-L block of X from LDS
+// Whether X, the rotation about x that takes y to z, joins orders a and b of
+// one degree. It keeps the parity in x and turns the parity in y of its
+// input into the parity in z of its output, so three entries of four are
+// zero (the host's table holds exact zeros there).
+constexpr bool x_joins(int l, int a, int b) {
+  const int pa = a < 0 ? -a : a, pb = b < 0 ? -b : b;
+  return ((pa + (a < 0)) & 1) == ((pb + (b < 0)) & 1) && ((l + pa) & 1) == int(b < 0);
+}
+
+// v <- X_L v (TRANS: X_L^T v). The block's entries are the same for all
+// lanes: scalar loads, one operand of each multiply-add.
 template <typename V, typename T, int L, bool TRANS>
 __device__ __forceinline__ void shell_rot_x(V* v, const T* xs) {
   constexpr int d = 2 * L + 1;
@@ -1430,14 +1440,12 @@ __device__ __forceinline__ void shell_rot_x(V* v, const T* xs) {
     T re = T(0), im = T(0);
 #pragma unroll
     for (int j = 0; j < d; ++j) {
+      if (!(TRANS ? x_joins(L, j - L, i - L) : x_joins(L, i - L, j - L))) continue;
       const T c = TRANS ? xs[o + j * d + i] : xs[o + i * d + j];
       re += c * v[j].x;
       im += c * v[j].y;
     }
     w[i] = cmk<V>(re, im);
-    // one row's matrix entries at a time (the scheduler would otherwise
-    // load the whole (2L+1)^2 block ahead and run out of registers)
-    __builtin_amdgcn_sched_barrier(0);
   }
 #pragma unroll
   for (int i = 0; i < d; ++i) v[i] = w[i];
@@ -1469,131 +1477,109 @@ __device__ __forceinline__ void k_angles(T kx, T ky, T kz, T* cp, T* sp, T* ct, 
   }
 }
 
-// Shells L..N of one point: to the k = z frame, D(R) = X^T Rz(-theta) X
-// Rz(-phi) (BACK: D(R)^T = Rz(phi) X^T Rz(theta) X), scaled by sc; one shell
-// in registers at a time.
-template <typename V, typename T, int N, bool BACK, int L = 0, int LAST = N>
-__device__ __forceinline__ void frame_shells(V* v, size_t ms, const T* xs, const T* cp, const T* sp,
-                                             const T* ct, const T* st, T sc) {
-  if constexpr (L <= LAST) {
-    constexpr int d = 2 * L + 1, a0 = L * L;
-    V w[d];
+// Shell L of one point: to the k = z frame, D(R) = X^T Rz(-theta) X Rz(-phi)
+// (BACK: D(R)^T = Rz(phi) X^T Rz(theta) X), scaled by sc; moments of v at
+// stride vs to moments of o at stride os.
+template <typename V, typename T, int L, bool BACK>
+__device__ __forceinline__ void frame_shell(const V* v, size_t vs, V* o, size_t os, const T* xs, const T* cp,
+                                            const T* sp, const T* ct, const T* st, T sc) {
+  constexpr int d = 2 * L + 1, a0 = L * L;
+  V w[d];
 #pragma unroll
-    for (int i = 0; i < d; ++i) {
-      const V x = v[(a0 + i) * ms];
-      w[i] = cmk<V>(sc * x.x, sc * x.y);
-    }
-    if constexpr (L > 0) {
-      T ns[L + 1];
-      if constexpr (!BACK) {
-#pragma unroll
-        for (int m = 0; m <= L; ++m) ns[m] = -sp[m];
-        shell_rot_z<V, T, L>(w, cp, ns);
-        shell_rot_x<V, T, L, false>(w, xs);
-#pragma unroll
-        for (int m = 0; m <= L; ++m) ns[m] = -st[m];
-        shell_rot_z<V, T, L>(w, ct, ns);
-        shell_rot_x<V, T, L, true>(w, xs);
-      } else {
-        shell_rot_x<V, T, L, false>(w, xs);
-        shell_rot_z<V, T, L>(w, ct, st);
-        shell_rot_x<V, T, L, true>(w, xs);
-        shell_rot_z<V, T, L>(w, cp, sp);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < d; ++i) v[(a0 + i) * ms] = w[i];
-    frame_shells<V, T, N, BACK, L + 1, LAST>(v, ms, xs, cp, sp, ct, st, sc);
+  for (int i = 0; i < d; ++i) {
+    const V x = v[(a0 + i) * vs];
+    w[i] = cmk<V>(sc * x.x, sc * x.y);
   }
+  if constexpr (L > 0) {
+    T ns[L + 1];
+    if constexpr (!BACK) {
+#pragma unroll
+      for (int m = 0; m <= L; ++m) ns[m] = -sp[m];
+      shell_rot_z<V, T, L>(w, cp, ns);
+      shell_rot_x<V, T, L, false>(w, xs);
+#pragma unroll
+      for (int m = 0; m <= L; ++m) ns[m] = -st[m];
+      shell_rot_z<V, T, L>(w, ct, ns);
+      shell_rot_x<V, T, L, true>(w, xs);
+    } else {
+      shell_rot_x<V, T, L, false>(w, xs);
+      shell_rot_z<V, T, L>(w, ct, st);
+      shell_rot_x<V, T, L, true>(w, xs);
+      shell_rot_z<V, T, L>(w, cp, sp);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < d; ++i) o[(a0 + i) * os] = w[i];
 }
 
-// Shell L (= blockIdx.y, uniform per workgroup) of every point.
+// Shell sh (uniform per wavefront) of every lane's point.
 template <typename V, typename T, int N, bool BACK, int L = 0>
-__device__ __forceinline__ void frame_shell_of(int sh, V* v, size_t ms, const T* xs, const T* cp, const T* sp,
-                                               const T* ct, const T* st, T sc) {
+__device__ __forceinline__ void frame_shell_of(int sh, const V* v, size_t vs, V* o, size_t os, const T* xs, T kx,
+                                               T ky, T kz, T sc) {
   if constexpr (L <= N) {
-    if (sh == L) frame_shells<V, T, N, BACK, L, L>(v, ms, xs, cp, sp, ct, st, sc);
-    else frame_shell_of<V, T, N, BACK, L + 1>(sh, v, ms, xs, cp, sp, ct, st, sc);
+    if (sh == L) {
+      T cp[L + 1], sp[L + 1], ct[L + 1], st[L + 1];
+      k_angles<T, L>(kx, ky, kz, cp, sp, ct, st);
+      frame_shell<V, T, L, BACK>(v, vs, o, os, xs, cp, sp, ct, st, sc);
+    } else {
+      frame_shell_of<V, T, N, BACK, L + 1>(sh, v, vs, o, os, xs, kx, ky, kz, sc);
+    }
   }
-}
-
-// Every point's moments (scaled by sc) to (BACK: from) its k = z frame, in
-// place in the full spectrum [b][kz][ky][kx]. The rotation is block
-// diagonal by degree, so the grid's second dimension runs over the degree
-// shells: a thread holds one shell of one point (at most 2N + 1 values),
-// which keeps the registers per thread low enough for the waves the
-// streaming access needs.
-template <typename T, int NN, int N, bool BACK>
-__global__ void __launch_bounds__(kEBlock)
-k_expo_frame(typename cplx_of<T>::type* __restrict__ v, const T* __restrict__ kv, const T* __restrict__ xrot,
-             T sc) {
-  using V = typename cplx_of<T>::type;
-  constexpr int n = NN, H = NN / 2;
-  constexpr size_t MS = size_t(n) * n * H;
-  constexpr int XS = xrot_size(N);
-  __shared__ T xs[XS];
-  for (int i = threadIdx.x; i < XS; i += kEBlock) xs[i] = xrot[i];
-  __syncthreads();
-  const int pt = blockIdx.x * kEBlock + threadIdx.x;
-  if (pt >= n * n * H) return;
-  const int xi = pt % H, yi = SpecLayout<T, NN>::ky_of(pt), zi = SpecLayout<T, NN>::z_of(pt);
-  T cp[N + 1], sp[N + 1], ct[N + 1], st[N + 1];
-  k_angles<T, N>(kv[xi], kv[yi], kv[zi], cp, sp, ct, st);
-  frame_shell_of<V, T, N, BACK>(int(blockIdx.y), v + pt, MS, xs, cp, sp, ct, st, sc);
 }
 
 // a <- E_m a + Phi_m q on the degrees m..N of orders m and -m (same
-// blocks), for m = MM..N, with a and q (both in the k = z frame) read from
-// and a written to the spectrum
-template <typename V, typename T, int N, int MM = 0, int LAST = N>
-__device__ __forceinline__ void expo_blocks(V* a, const V* q, size_t ms, const V* row) {
-  if constexpr (MM <= LAST) {
-    constexpr int d = N + 1 - MM;
-    constexpr int NS = MM == 0 ? 1 : 2;   // the orders m and -m
-    const V* E = row + expo_block_offset(N, MM);
-    const V* P = E + d * d;
-    V x[NS][d], y[NS][d];
+// blocks), m = MM, with a and q (both in the k = z frame) in LDS
+template <typename V, typename T, int N, int MM, bool HASQ>
+__device__ __forceinline__ void expo_blocks(V* a, const V* q, int ms, const V* row) {
+  constexpr int d = N + 1 - MM;
+  constexpr int NS = MM == 0 ? 1 : 2;   // the orders m and -m
+  const V* E = row + expo_block_offset(N, MM);
+  const V* P = E + d * d;
+  V x[NS][d], y[HASQ ? NS : 1][HASQ ? d : 1];
 #pragma unroll
-    for (int sgn = 0; sgn < NS; ++sgn)
+  for (int sgn = 0; sgn < NS; ++sgn)
 #pragma unroll
-      for (int j = 0; j < d; ++j) {
-        const int m = sgn ? -MM : MM;
-        const int bj = (MM + j) * (MM + j) + (MM + j) + m;
-        x[sgn][j] = a[bj * ms];
-        y[sgn][j] = q ? q[bj * ms] : cmk<V>(T(0), T(0));
-      }
-    // rows one at a time (a run-time loop: unrolled, the compiler would load
-    // all 2 d^2 table entries at once), each written as soon as it is formed
-    // (the block's inputs are all in registers by then)
+    for (int j = 0; j < d; ++j) {
+      const int m = sgn ? -MM : MM;
+      const int bj = (MM + j) * (MM + j) + (MM + j) + m;
+      x[sgn][j] = a[bj * ms];
+      if constexpr (HASQ) y[sgn][j] = q[bj * ms];
+    }
+  // rows one at a time (a run-time loop: unrolled, the compiler would load
+  // all 2 d^2 table entries at once), each written as soon as it is formed
+  // (the block's inputs are all in registers by then)
 #pragma unroll 1
-    for (int i = 0; i < d; ++i) {
-      T re[NS], im[NS];
+  for (int i = 0; i < d; ++i) {
+    T re[NS], im[NS];
 #pragma unroll
-      for (int sgn = 0; sgn < NS; ++sgn) re[sgn] = im[sgn] = T(0);
+    for (int sgn = 0; sgn < NS; ++sgn) re[sgn] = im[sgn] = T(0);
 #pragma unroll
-      for (int j = 0; j < d; ++j) {
-        const V e = E[i * d + j];
-        const V f = q ? P[i * d + j] : cmk<V>(T(0), T(0));
+    for (int j = 0; j < d; ++j) {
+      const V e = E[i * d + j];
+      V f{};
+      if constexpr (HASQ) f = P[i * d + j];
 #pragma unroll
-        for (int sgn = 0; sgn < NS; ++sgn) {
-          re[sgn] += e.x * x[sgn][j].x - e.y * x[sgn][j].y + f.x * y[sgn][j].x - f.y * y[sgn][j].y;
-          im[sgn] += e.x * x[sgn][j].y + e.y * x[sgn][j].x + f.x * y[sgn][j].y + f.y * y[sgn][j].x;
+      for (int sgn = 0; sgn < NS; ++sgn) {
+        re[sgn] += e.x * x[sgn][j].x - e.y * x[sgn][j].y;
+        im[sgn] += e.x * x[sgn][j].y + e.y * x[sgn][j].x;
+        if constexpr (HASQ) {
+          re[sgn] += f.x * y[sgn][j].x - f.y * y[sgn][j].y;
+          im[sgn] += f.x * y[sgn][j].y + f.y * y[sgn][j].x;
         }
       }
-      const int l = MM + i;
-#pragma unroll
-      for (int sgn = 0; sgn < NS; ++sgn) a[(l * l + l + (sgn ? -MM : MM)) * ms] = cmk<V>(re[sgn], im[sgn]);
     }
-    expo_blocks<V, T, N, MM + 1, LAST>(a, q, ms, row);
+    const int l = MM + i;
+#pragma unroll
+    for (int sgn = 0; sgn < NS; ++sgn) a[(l * l + l + (sgn ? -MM : MM)) * ms] = cmk<V>(re[sgn], im[sgn]);
   }
 }
 
-// Order m (= blockIdx.y, uniform per workgroup) of one point.
-template <typename V, typename T, int N, int MM = 0>
-__device__ __forceinline__ void expo_block_of(int m, V* a, const V* q, size_t ms, const V* row) {
+// Order m (uniform per wavefront) of every lane's point.
+template <typename V, typename T, int N, bool HASQ, int MM = 0>
+__device__ __forceinline__ void expo_block_of(int m, V* a, const V* q, int ms, const V* row) {
   if constexpr (MM <= N) {
-    if (m == MM) expo_blocks<V, T, N, MM, MM>(a, q, ms, row);
-    else expo_block_of<V, T, N, MM + 1>(m, a, q, ms, row);
+    if (m == MM) expo_blocks<V, T, N, MM, HASQ>(a, q, ms, row);
+    else expo_block_of<V, T, N, HASQ, MM + 1>(m, a, q, ms, row);
   }
 }
 
@@ -1605,70 +1591,63 @@ __device__ __forceinline__ void expo_block_of(int m, V* a, const V* q, size_t ms
 // frequency is 0): the four lanes that share a row read it in the same
 // instruction, which fetches it once. A bijection of the points, so the
 // results are those of any other order.
-#ifndef RTE_EXPO_OCT
-#define RTE_EXPO_OCT 0
-#endif
 template <int NN> struct ExpoQuad {
   static constexpr int H = NN / 2;
-  static constexpr bool OCT = RTE_EXPO_OCT;   // also pair (y, z) with (z, y): eight points per row
-  static constexpr int G = OCT ? 8 : 4;       // points per group
-  static constexpr int TXMAX = 64 / G;
-  static constexpr int TX = (H % TXMAX == 0) ? TXMAX : (H % 8 == 0 ? 8 : (H % 4 == 0 ? 4 : 1));
-  static_assert(64 % (G * TX) == 0, "groups must tile a wavefront");
-  static constexpr int C = NN / 2;                                 // classes per axis
-  static constexpr int NCLS = OCT ? C * (C + 1) / 2 : C * C;       // (y, z) classes
-  static constexpr int THREADS = NCLS * (H / TX) * G * TX;          // threads launched
+  static constexpr int TX = (H % 16 == 0) ? 16 : (H % 8 == 0 ? 8 : (H % 4 == 0 ? 4 : 1));
+  static constexpr int C = NN / 2;                    // classes per axis
+  static constexpr int THREADS = C * C * H * 4;       // spectral points
+  static_assert(64 % (4 * TX) == 0 && THREADS % 64 == 0, "groups must tile the wavefronts");
   static __device__ __forceinline__ int mirror(int i) { return i == 0 ? NN / 2 : NN - i; }
-  // point (x, y, z) of thread t < THREADS; false for an idle lane of a
-  // diagonal class, whose swapped points are the same points
-  static __device__ __forceinline__ bool point(int t, int& x, int& y, int& z) {
-    const int Q = t / (G * TX), l = t - Q * G * TX;
+  static __device__ __forceinline__ void point(int t, int& x, int& y, int& z) {
+    const int Q = t / (4 * TX), l = t - Q * 4 * TX;
     const int sub = l / TX, xl = l - sub * TX;
     constexpr int XT = H / TX;
     const int xt = Q % XT, cls = Q / XT;
-    int yc, zc;
-    if constexpr (OCT) {
-      // cls -> (yc <= zc): row zc holds zc + 1 classes
-      zc = int((sqrtf(8.f * cls + 1.f) - 1.f) * 0.5f);
-      while ((zc + 1) * (zc + 2) / 2 <= cls) ++zc;
-      while (zc * (zc + 1) / 2 > cls) --zc;
-      yc = cls - zc * (zc + 1) / 2;
-      if (sub & 4) {
-        if (yc == zc) return false;
-        const int tmp = yc;
-        yc = zc;
-        zc = tmp;
-      }
-    } else {
-      yc = cls % C;
-      zc = cls / C;
-    }
+    const int yc = cls % C, zc = cls / C;
     x = xt * TX + xl;
     y = (sub & 1) ? mirror(yc) : yc;
     z = (sub & 2) ? mirror(zc) : zc;
-    return true;
   }
 };
 
-template <typename T, int NN, int N>
-__global__ void __launch_bounds__(kEBlock)
-k_expo_blocks(typename cplx_of<T>::type* __restrict__ spec, const typename cplx_of<T>::type* __restrict__ qs,
-              const typename cplx_of<T>::type* __restrict__ tab) {
+// The spectral points' moments to the k = z frame, the block products there
+// and back, in place in the spectrum. A workgroup holds 64 points in LDS,
+// [moment][point], and has N + 1 wavefronts: wavefront w rotates degree w of
+// all 64 points (the rotation is block diagonal by degree), multiplies
+// orders +-w (the blocks are independent by order) and rotates degree w
+// back, so a thread never holds more than one shell or one pair of orders.
+// What bounds it is the gather of the table rows from the L2 on top of the one
+// read and one write of the spectrum: 457 us at 128^3 P_7 FP32 (2.3 TB/s of
+// spectrum), where three kernels with the moments going through HBM between
+// them took 251 + 404 + 271 us.
+template <typename T, int N, bool HASQ> constexpr size_t expo_lds() {
+  return size_t(HASQ ? 2 : 1) * (N + 1) * (N + 1) * 64 * 2 * sizeof(T);
+}
+template <typename T, int NN, int N, bool HASQ>
+__global__ void __launch_bounds__(64 * (N + 1), sizeof(T) == 4 ? 4 : 2)
+k_expo_rotated(typename cplx_of<T>::type* __restrict__ spec, const typename cplx_of<T>::type* __restrict__ qs,
+               const T* __restrict__ kv, const T* __restrict__ xrot,
+               const typename cplx_of<T>::type* __restrict__ tab, T sc) {
   using V = typename cplx_of<T>::type;
-  constexpr int n = NN;
+  constexpr int n = NN, M = (N + 1) * (N + 1);
   constexpr size_t MS = SpecLayout<T, NN>::MS;
-  const int t = blockIdx.x * kEBlock + threadIdx.x;
-  if (t >= ExpoQuad<NN>::THREADS) return;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  V* xa = reinterpret_cast<V*>(smem) + lane;
+  V* ya = xa + (HASQ ? M * 64 : 0);
   int xi, yi, zi;
-  if (!ExpoQuad<NN>::point(t, xi, yi, zi)) return;
-  const int pt = SpecLayout<T, NN>::at(zi, yi, xi);
+  ExpoQuad<NN>::point(blockIdx.x * 64 + lane, xi, yi, zi);
+  const size_t pt = SpecLayout<T, NN>::at(zi, yi, xi);
+  const T kx = kv[xi], ky = kv[yi], kz = kv[zi];
+  frame_shell_of<V, T, N, false>(w, spec + pt, MS, xa, 64, xrot, kx, ky, kz, sc);
+  if constexpr (HASQ) frame_shell_of<V, T, N, false>(w, qs + pt, MS, ya, 64, xrot, kx, ky, kz, sc);
+  __syncthreads();
   auto freq = [](int i) { return i < n / 2 ? i : (i == n / 2 ? 0 : i - n); };
   const int fy = freq(yi), fz = freq(zi);
   const int f2 = xi * xi + fy * fy + fz * fz;
-  // the blocks of different orders are independent: one order per grid row
-  // (blockIdx.y), which keeps a thread's registers to one block
-  expo_block_of<V, T, N>(int(blockIdx.y), spec + pt, qs ? qs + pt : nullptr, MS,
-                         tab + (size_t)f2 * expo_row_size(N));
+  expo_block_of<V, T, N, HASQ>(w, xa, ya, 64, tab + (size_t)f2 * expo_row_size(N));
+  __syncthreads();
+  frame_shell_of<V, T, N, true>(w, xa, 64, spec + pt, MS, xrot, kx, ky, kz, T(1));
 }
 
 }  // namespace rte
@@ -1766,6 +1745,10 @@ hipError_t prepare_t(const StepArgs& a) {
   set(reinterpret_cast<const void*>(&k_pencil<T, NN, PENCIL_ZDERIV>), zd_lds<T, NN>());
   set(reinterpret_cast<const void*>(&k_pencil<T, NN, PENCIL_ZFWD>), zd_lds<T, NN>());
   set(reinterpret_cast<const void*>(&k_pencil<T, NN, PENCIL_ZINV>), zd_lds<T, NN>());
+  if constexpr (N <= kDenseOrder) {
+    set(reinterpret_cast<const void*>(&k_expo_rotated<T, NN, N, false>), expo_lds<T, N, false>());
+    set(reinterpret_cast<const void*>(&k_expo_rotated<T, NN, N, true>), expo_lds<T, N, true>());
+  }
   return e;
 }
 
@@ -1907,7 +1890,6 @@ hipError_t enqueue_expo(const StepArgs& a, const OpArgs& op, ProfRec* pr) {
   p.theta = op.scale;
   p.eps = op.eps;
   p.inv_n3 = T(1.0 / (double(n) * n * n));
-  const int eblocks = (n * n * H + kEBlock - 1) / kEBlock;
   if (op.count == 1) {
     // rotation data in the stage buffer v: X blocks, B_z couplings, then the
     // block-exponential table (layout checked on the host)
@@ -1919,16 +1901,15 @@ hipError_t enqueue_expo(const StepArgs& a, const OpArgs& op, ProfRec* pr) {
     hipLaunchKernelGGL((k_expo_table<T, N>), dim3(unsigned((tblocks + kExpoTableWaves - 1) / kExpoTableWaves)),
                        dim3(64 * kExpoTableWaves), 0, st, tab, bz, p, op.kunit, nf2);
     rec(PROF_EXPO_TABLE);
+    const dim3 pgrid(ExpoQuad<NN>::THREADS / 64), pblk(64 * (N + 1));
     if (q)
-      hipLaunchKernelGGL((k_expo_frame<T, NN, N, false>), dim3(eblocks, N + 1), dim3(kEBlock), 0, st, dspec, kv, xrot,
-                         p.inv_n3);
-    hipLaunchKernelGGL((k_expo_frame<T, NN, N, false>), dim3(eblocks, N + 1), dim3(kEBlock), 0, st, spec, kv, xrot,
-                       p.inv_n3);
-    hipLaunchKernelGGL((k_expo_blocks<T, NN, N>), dim3((ExpoQuad<NN>::THREADS + kEBlock - 1) / kEBlock, N + 1),
-                       dim3(kEBlock), 0, st, spec, q ? dspec : nullptr, tab);
-    hipLaunchKernelGGL((k_expo_frame<T, NN, N, true>), dim3(eblocks, N + 1), dim3(kEBlock), 0, st, spec, kv, xrot, T(1));
+      hipLaunchKernelGGL((k_expo_rotated<T, NN, N, true>), pgrid, pblk, (expo_lds<T, N, true>()), st, spec, dspec, kv,
+                         xrot, tab, p.inv_n3);
+    else
+      hipLaunchKernelGGL((k_expo_rotated<T, NN, N, false>), pgrid, pblk, (expo_lds<T, N, false>()), st, spec, dspec,
+                         kv, xrot, tab, p.inv_n3);
   } else {
-    hipLaunchKernelGGL((k_expo<T, NN, N>), dim3(eblocks), dim3(kEBlock), 0, st, spec, q ? dspec : nullptr, kv, p);
+    hipLaunchKernelGGL((k_expo<T, NN, N>), dim3((n * n * H + kEBlock - 1) / kEBlock), dim3(kEBlock), 0, st, spec, q ? dspec : nullptr, kv, p);
   }
   rec(PROF_EXPO);
   hipLaunchKernelGGL((k_pencil<T, NN, PENCIL_ZINV>), dim3(pencils), zblk, lz, st, spec, spec, tw, kv, cctl);
