@@ -592,6 +592,8 @@ enum { EPI_MID = 0, EPI_FIRST = 1, EPI_LAST = 2, EPI_ADJ = 3, EPI_EULER = 4, EPI
 
 // Pointwise epilogue of RB rows starting at row y0 of plane (b, z), on
 // (x_{2j}, x_{2j+1}) pairs:
+// (w: the transformed streaming term times ws, the scale that the streaming pass
+// left out; 1 after the coupling passes)
 //   forward stages  o = u + w + h (-Sigma_l v + q)   -> dst
 //     (EPI_FIRST: v = u; EPI_LAST: also phi_int += dt o (FP64) for the
 //     fluence moment and the partial sums of (o - u)^2 and o^2);
@@ -607,7 +609,7 @@ enum { EPI_MID = 0, EPI_FIRST = 1, EPI_LAST = 2, EPI_ADJ = 3, EPI_EULER = 4, EPI
 template <typename V, typename T, int NN, int RB, typename Lay, int BLOCK, int MODE, bool KEEP = false>
 __device__ __forceinline__ void epilogue(V* pl, int y0, int b, int z, const T* vin, T* u,
                                          T* dst, const T* __restrict__ sig, const T* __restrict__ q,
-                                         bool hasq, T qs, double* __restrict__ phi_int, T h, double dt,
+                                         bool hasq, T qs, double* __restrict__ phi_int, T h, T ws, double dt,
                                          double& acc_d, double& acc_o) {
   constexpr int n = NN, H = NN / 2;
   const int l = isqrt_c(b);
@@ -633,17 +635,17 @@ __device__ __forceinline__ void epilogue(V* pl, int y0, int b, int z, const T* v
       src1 += qs * qq.y;
     }
     if constexpr (MODE == EPI_APPLY) {
-      *reinterpret_cast<V*>(dst + poff + e) = cmk<V>(-w.x + ss.x * vv.x, -w.y + ss.y * vv.y);
+      *reinterpret_cast<V*>(dst + poff + e) = cmk<V>(ss.x * vv.x - ws * w.x, ss.y * vv.y - ws * w.y);
       continue;
     }
     if constexpr (MODE == EPI_ADJ || MODE == EPI_ADJL) {
-      const V o = cmk<V>(w.x + h * src0, w.y + h * src1);
+      const V o = cmk<V>(ws * w.x + h * src0, ws * w.y + h * src1);
       if constexpr (MODE == EPI_ADJ) *reinterpret_cast<V*>(dst + poff + e) = o;
       *reinterpret_cast<V*>(u + poff + e) = cmk<V>(uu.x + o.x, uu.y + o.y);
       if constexpr (KEEP) pl[Lay::pos(y, j)] = o;
       continue;
     }
-    const V o = cmk<V>(uu.x + w.x + h * src0, uu.y + w.y + h * src1);
+    const V o = cmk<V>(uu.x + ws * w.x + h * src0, uu.y + ws * w.y + h * src1);
     *reinterpret_cast<V*>(dst + poff + e) = o;
     if constexpr (KEEP) pl[Lay::pos(y, j)] = o;   // the output plane, for the fused forward transform
     if ((MODE == EPI_LAST || MODE == EPI_EULER) && b == 0) {
@@ -705,7 +707,7 @@ __global__ void __launch_bounds__(kZBlock)
 k_rows_inv(const typename cplx_of<T>::type* spec, const T* vin, T* u, T* dst,
            const T* __restrict__ sig, const T* __restrict__ q, const int* __restrict__ qflag,
            double* __restrict__ phi_int, double* __restrict__ partial,
-           const typename cplx_of<T>::type* __restrict__ twg, int M, T h, double dt,
+           const typename cplx_of<T>::type* __restrict__ twg, int M, T h, T ws, double dt,
            const Ctl* __restrict__ ctl, int stage, long long step1, typename cplx_of<T>::type* fspec = nullptr) {
   using V = typename cplx_of<T>::type;
   constexpr int n = NN, H = NN / 2, RB = RowShape<NN>::RB, NB = NN / RB;
@@ -733,7 +735,7 @@ k_rows_inv(const typename cplx_of<T>::type* spec, const T* vin, T* u, T* dst,
   double acc_d = 0.0, acc_o = 0.0;
   const bool hasq = (q != nullptr) && qflag[b * n + z];
   const T qs = hasq ? T(source_weight(ctl, stage, step1)) : T(0);
-  epilogue<V, T, NN, RB, Lay, kZBlock, MODE, FUSE>(pl, y0, b, z, vin, u, dst, sig, q, hasq, qs, phi_int, h, dt,
+  epilogue<V, T, NN, RB, Lay, kZBlock, MODE, FUSE>(pl, y0, b, z, vin, u, dst, sig, q, hasq, qs, phi_int, h, ws, dt,
                                                   acc_d, acc_o);
   if constexpr (FUSE) {
     __syncthreads();
@@ -1699,7 +1701,7 @@ void launch_fwd_plane(hipStream_t st, const T* src, typename cplx_of<T>::type* s
 // Inverse plane pass of all M n planes with epilogue MODE on `ns` slot rows.
 template <typename T, int NN, int MODE, bool FUSE>
 void launch_plane(const StepArgs& a, const typename cplx_of<T>::type* spec, const T* src, T* u, T* out, const T* q, int M,
-                  double hs, int stage, long long step1, unsigned ns, long long bs) {
+                  double hs, double ws, int stage, long long step1, unsigned ns, long long bs) {
   using V = typename cplx_of<T>::type;
   hipStream_t st = reinterpret_cast<hipStream_t>(a.stream);
   const T* sig = static_cast<const T*>(a.sig);
@@ -1708,7 +1710,7 @@ void launch_plane(const StepArgs& a, const typename cplx_of<T>::type* spec, cons
   V* fspec = FUSE ? static_cast<V*>(a.spec) : nullptr;
   using C = pln::Cfg<T, NN>;
   hipLaunchKernelGGL((pln::k_plane<T, NN, MODE, FUSE>), dim3(M * NN / C::PPW, ns), dim3(C::BT), C::lds(), st, spec, src,
-                     u, out, sig, q, a.qflag, a.phi_int, a.partial, tw, M, T(hs), a.dt, cctl, stage, step1, fspec, bs);
+                     u, out, sig, q, a.qflag, a.phi_int, a.partial, tw, M, T(hs), T(ws), a.dt, cctl, stage, step1, fspec, bs);
 }
 
 // Grids up to 128 points per axis keep a whole plane in LDS (plane passes);
@@ -1809,10 +1811,12 @@ void enqueue_stage(const StepArgs& a, ProfRec* pr, double hs, double sgn, const 
     rec(PROF_FWD_PLANE);
   }
   V* coupled = dspec;   // the inverse passes read the coupled spectrum from here
+  double ws = 1.0;      // and scale it by this
   if constexpr (strm::use_stream<T, NN, N>()) {
     using C = strm::Cfg<T, NN, N>;
     hipLaunchKernelGGL((strm::k_stream<T, NN, N>), dim3(2 * NN * (NN / 2 / C::TZ), ns), dim3(C::BT), C::lds(), st,
-                       spec, dspec, tw, kv, T(sgn * hs / n2), cctl, bs);
+                       spec, dspec, tw, kv, cctl, bs);
+    ws = sgn * hs / n2 / strm::w_scale<NN>();
   } else {
     launch_pencil<T, NN, PENCIL_ZDERIV>(st, spec, dspec, tw, kv, cctl, M, ns, bs);
     rec(PROF_ZDERIV);
@@ -1830,11 +1834,11 @@ void enqueue_stage(const StepArgs& a, ProfRec* pr, double hs, double sgn, const 
     launch_pencil<T, NN, PENCIL_YINV>(st, coupled, coupled, tw, kv, cctl, M);
     rec(PROF_Y_INV);
     hipLaunchKernelGGL((k_rows_inv<T, NN, MODE, FUSE>), dim3(rblocks), zblk, lr, st, coupled, src, u, out, sig,
-                       q, a.qflag, a.phi_int, a.partial, tw, M, T(hs), a.dt, cctl, stage, step1,
+                       q, a.qflag, a.phi_int, a.partial, tw, M, T(hs), T(ws), a.dt, cctl, stage, step1,
                        FUSE ? spec : static_cast<V*>(nullptr));
     rec(PROF_INV_ROWS);
   } else {
-    launch_plane<T, NN, MODE, FUSE>(a, coupled, src, u, out, q, M, hs, stage, step1, ns, bs);
+    launch_plane<T, NN, MODE, FUSE>(a, coupled, src, u, out, q, M, hs, ws, stage, step1, ns, bs);
     rec(PROF_INV_PLANE);
   }
 }
@@ -1925,11 +1929,11 @@ hipError_t enqueue_expo(const StepArgs& a, const OpArgs& op, ProfRec* pr) {
     hipLaunchKernelGGL((k_pencil<T, NN, PENCIL_YINV>), dim3(pencils), zblk, lz, st, spec, spec, tw, kv, cctl);
     rec(PROF_Y_INV);
     hipLaunchKernelGGL((k_rows_inv<T, NN, EPI_SET, false>), dim3(rblocks), zblk, lr, st, spec, u, u, u, sig,
-                       static_cast<const T*>(nullptr), a.qflag, a.phi_int, a.partial, tw, M, T(0), 0.0, cctl, 0,
+                       static_cast<const T*>(nullptr), a.qflag, a.phi_int, a.partial, tw, M, T(0), T(1), 0.0, cctl, 0,
                        0LL);
     rec(PROF_INV_ROWS);
   } else {
-    launch_plane<T, NN, EPI_SET, false>(a, spec, u, u, u, nullptr, M, 0.0, 0, 0LL, 1, 0LL);
+    launch_plane<T, NN, EPI_SET, false>(a, spec, u, u, u, nullptr, M, 0.0, 1.0, 0, 0LL, 1, 0LL);
     rec(PROF_INV_PLANE);
   }
   return hipGetLastError();

@@ -253,7 +253,7 @@ template <typename T, int NN, int MODE, bool FUSE>
 __global__ void __launch_bounds__((Cfg<T, NN>::BT), (Cfg<T, NN>::waves()))
 k_plane(const typename cplx_of<T>::type* spec, const T* vin, T* u, T* dst, const T* __restrict__ sig,
         const T* __restrict__ q, const int* __restrict__ qflag, double* __restrict__ phi_int,
-        double* __restrict__ partial, const typename cplx_of<T>::type* __restrict__ twg, int M, T h, double dt,
+        double* __restrict__ partial, const typename cplx_of<T>::type* __restrict__ twg, int M, T h, T ws, double dt,
         const Ctl* __restrict__ ctl, int stage, long long step1, typename cplx_of<T>::type* fspec, long long bs) {
   using C = Cfg<T, NN>;
   using V = typename C::V;
@@ -415,9 +415,9 @@ k_plane(const typename cplx_of<T>::type* spec, const T* vin, T* u, T* dst, const
           } else {
             T s = -ss[k].v[w] * vv[k].v[w];
             if constexpr (!kAdj) s += of(pq, pp[k]) * qq[k].v[w];
-            if constexpr (MODE == EPI_APPLY) o.v[w] = -x + ss[k].v[w] * vv[k].v[w];
-            else if constexpr (kAdj) o.v[w] = x + h * s;
-            else o.v[w] = uu[k].v[w] + x + h * s;
+            if constexpr (MODE == EPI_APPLY) o.v[w] = ss[k].v[w] * vv[k].v[w] - ws * x;
+            else if constexpr (kAdj) o.v[w] = ws * x + h * s;
+            else o.v[w] = uu[k].v[w] + ws * x + h * s;
           }
         }
         if constexpr (MODE != EPI_ADJL) *reinterpret_cast<I*>(dst + po[k]) = o;

@@ -2,8 +2,14 @@
 // spectrum (orders up to kDenseOrder).
 //
 // Per spectral point the streaming term of eq. (10) in the real basis is
-//   W_a = s * ( -i (kx Bx + ky By)[a,b] S_b  -  Bz[a,b] dS_b/dz ),
-// S the moments' xy spectra [b][z][ky][kx]. Every B_j moves degree l to
+//   W_a = -i (kx Bx + ky By)[a,b] S_b  -  Bz[a,b] dS_b/dz,
+// S the moments' xy spectra [b][z][ky][kx]. The stage's scale is left to the
+// epilogue of the inverse pass, which multiplies and adds in one rounding. Folded
+// into k here, the rounding of every product would enter all steps alike and add
+// up over a solve: geometric mean of the errors of 41 FP32 solves against 64 bits
+// 1.577e-7, 1.505e-7 with the scale left out (1.562e-7 with the two passes). (W
+// carries 2^-2 ceil(log2 n) instead, which rounds nothing and keeps the range of a
+// scaled one.) Every B_j moves degree l to
 // l +- 1 (eq. 6), so the rows of even degree read the odd degrees only and
 // the other way round: the operator splits into two halves that share no
 // input and no output. A workgroup owns one half Q (inputs of degree parity
@@ -254,10 +260,10 @@ struct Scatter {
   }
 };
 
-// X = -i s kx S_b (S: VW points), Y the same with ky, Z = -s dS_b/dz from LDS.
+// X = -i kx S_b (S: VW points), Y the same with ky, Z = -dS_b/dz from LDS.
 template <class C, typename T, int N, int B>
 __device__ __forceinline__ void add_moment(typename C::V (*acc)[C::VW], const typename C::V* S, const typename C::V* d,
-                                           const T* skx, T sky) {
+                                           const T* kxs, T kys) {
   using V = typename C::V;
   V X[C::VW], Y[C::VW], Z[C::VW];
   if constexpr (C::VW == 2) {
@@ -270,8 +276,8 @@ __device__ __forceinline__ void add_moment(typename C::V (*acc)[C::VW], const ty
 #pragma unroll
   for (int v = 0; v < C::VW; ++v) {
     const V s = cmk<V>(S[v].y, -S[v].x);
-    Y[v] = cscale(s, sky);
-    X[v] = cscale(s, skx[v]);
+    Y[v] = cscale(s, kys);
+    X[v] = cscale(s, kxs[v]);
   }
   Scatter<C, T, N, B, 0>::run(acc, X, Y, Z);
 }
@@ -302,15 +308,15 @@ __device__ __forceinline__ void load_s(typename C::V (*sv)[C::PPT / C::VW][C::VW
 template <class C, typename T, int N, int Q, int RD, int I0, int NM, int I = 0>
 __device__ __forceinline__ void add_s(typename C::V (*acc)[set_size(N, 1 - Q)][C::VW],
                                       const typename C::V (*sv)[C::PPT / C::VW][C::VW], const typename C::V* pub, int e,
-                                      const T* skx, T sky) {
+                                      const T* kxs, T kys) {
   constexpr int i = RD * C::MPR + I0 + I;
   if constexpr (I < NM && I0 + I < C::MPR && i < set_size(N, Q)) {
 #pragma unroll
     for (int k = 0; k < C::PPT / C::VW; ++k)
-      add_moment<C, T, N, set_at(N, Q, i)>(acc[k], sv[I][k], pub + (I0 + I) * C::SLOT + e + k * C::BT * C::VW, skx, sky);
+      add_moment<C, T, N, set_at(N, Q, i)>(acc[k], sv[I][k], pub + (I0 + I) * C::SLOT + e + k * C::BT * C::VW, kxs, kys);
     // (else the LDS reads of the whole round are hoisted above the sums)
     if constexpr (I % 2 == 1) __builtin_amdgcn_sched_barrier(0);
-    add_s<C, T, N, Q, RD, I0, NM, I + 1>(acc, sv, pub, e, skx, sky);
+    add_s<C, T, N, Q, RD, I0, NM, I + 1>(acc, sv, pub, e, kxs, kys);
   }
 }
 // Batches I0.. of a round after the first
@@ -318,21 +324,21 @@ template <class C, typename T, int N, int Q, int RD, int I0>
 __device__ __forceinline__ void add_batches(typename C::V (*acc)[set_size(N, 1 - Q)][C::VW],
                                             typename C::V (*sv)[C::PPT / C::VW][C::VW],
                                             const typename C::V* __restrict__ src, const typename C::V* pub, int e,
-                                            unsigned lo, const T* skx, T sky) {
+                                            unsigned lo, const T* kxs, T kys) {
   if constexpr (I0 < C::MPR && RD * C::MPR + I0 < set_size(N, Q)) {
     if constexpr (C::SG) {
       if constexpr (I0 > 0) load_s<C, N, Q, RD, I0, C::SB>(sv, src, lo);
-      add_s<C, T, N, Q, RD, I0, C::SB>(acc, sv, pub, e, skx, sky);
+      add_s<C, T, N, Q, RD, I0, C::SB>(acc, sv, pub, e, kxs, kys);
       __builtin_amdgcn_sched_barrier(0);
-      add_batches<C, T, N, Q, RD, I0 + C::SB>(acc, sv, src, pub, e, lo, skx, sky);
+      add_batches<C, T, N, Q, RD, I0 + C::SB>(acc, sv, src, pub, e, lo, kxs, kys);
     } else {
       typename C::V s1[1][C::PPT / C::VW][C::VW];
 #pragma unroll
       for (int k = 0; k < C::PPT / C::VW; ++k)
         load_points<C>(s1[0][k], pub + I0 * C::SLOT + C::DROWS * C::TZ + e + k * C::BT * C::VW);
-      add_s<C, T, N, Q, RD, I0, 1>(acc, s1, pub, e, skx, sky);
+      add_s<C, T, N, Q, RD, I0, 1>(acc, s1, pub, e, kxs, kys);
       if constexpr (I0 % 2 == 1) __builtin_amdgcn_sched_barrier(0);
-      add_batches<C, T, N, Q, RD, I0 + 1>(acc, sv, src, pub, e, lo, skx, sky);
+      add_batches<C, T, N, Q, RD, I0 + 1>(acc, sv, src, pub, e, lo, kxs, kys);
     }
   }
 }
@@ -376,7 +382,7 @@ __device__ __forceinline__ void load_tile(typename C::V* x, const typename C::V*
 template <class C, typename T, int N, int Q, int RD>
 __device__ __forceinline__ void rounds(typename C::V (*acc)[set_size(N, 1 - Q)][C::VW], typename C::V* x,
                                        const typename C::V* __restrict__ src, typename C::V* pub,
-                                       const typename C::V* tw, const T* kz, const T* skx, T sky, int g, int gl) {
+                                       const typename C::V* tw, const T* kz, const T* kxs, T kys, int g, int gl) {
   using V = typename C::V;
   constexpr int IN = set_size(N, Q);
   if constexpr (RD * C::MPR < IN) {
@@ -416,7 +422,7 @@ __device__ __forceinline__ void rounds(typename C::V (*acc)[set_size(N, 1 - Q)][
     if constexpr (C::SG) load_s<C, N, Q, RD, 0, C::SB>(sv, src, lo);
     load_tile<C, N, Q, RD + 1>(x, src, g, gl);
     lds_barrier();
-    add_batches<C, T, N, Q, RD, 0>(acc, sv, src, pub, e, lo, skx, sky);
+    add_batches<C, T, N, Q, RD, 0>(acc, sv, src, pub, e, lo, kxs, kys);
     // the sums are formed here (the compiler would sink them to the stores
     // and hold the published values of every round instead)
 #pragma unroll
@@ -426,13 +432,13 @@ __device__ __forceinline__ void rounds(typename C::V (*acc)[set_size(N, 1 - Q)][
 #pragma unroll
         for (int v = 0; v < C::VW; ++v) asm volatile("" : "+v"(acc[k][a][v].x), "+v"(acc[k][a][v].y));
     lds_barrier();
-    rounds<C, T, N, Q, RD + 1>(acc, x, src, pub, tw, kz, skx, sky, g, gl);
+    rounds<C, T, N, Q, RD + 1>(acc, x, src, pub, tw, kz, kxs, kys, g, gl);
   }
 }
 
 template <class C, typename T, int N, int Q>
 __device__ __forceinline__ void sweep(const typename C::V* __restrict__ src, typename C::V* __restrict__ dst,
-                                      typename C::V* pub, const typename C::V* tw, const T* kz, const T* skx, T sky) {
+                                      typename C::V* pub, const typename C::V* tw, const T* kz, const T* kxs, T kys) {
   using V = typename C::V;
   constexpr int OUTQ = set_size(N, 1 - Q);
   if constexpr (OUTQ > 0) {
@@ -448,7 +454,7 @@ __device__ __forceinline__ void sweep(const typename C::V* __restrict__ src, typ
         for (int v = 0; v < C::VW; ++v) acc[k][a][v] = cmk<V>(T(0), T(0));
     V x[C::P];
     load_tile<C, N, Q, 0>(x, src, g, tid % C::G);
-    rounds<C, T, N, Q, 0>(acc, x, src, pub, tw, kz, skx, sky, g, tid % C::G);
+    rounds<C, T, N, Q, 0>(acc, x, src, pub, tw, kz, kxs, kys, g, tid % C::G);
     const int e = tid * C::VW;
     const unsigned lo = unsigned(e / C::TZ) * unsigned(C::Lay::ZS) + e % C::TZ;
 #pragma unroll
@@ -463,15 +469,23 @@ __device__ __forceinline__ void sweep(const typename C::V* __restrict__ src, typ
   }
 }
 
-// Grid: (ky, kx tile, Q), neighbouring tiles on one XCD. sc: the factor s.
+// W's power-of-two scale, about 1 / n^2
+template <int NN> constexpr double w_scale() {
+  double s = 1.0;
+  for (int m = 1; m < NN; m *= 2) s *= 0.25;
+  return s;
+}
+
+// Grid: (ky, kx tile, Q), neighbouring tiles on one XCD.
 template <typename T, int NN, int N>
 __global__ void __launch_bounds__((Cfg<T, NN, N>::BT), (Cfg<T, NN, N>::min_waves()))
 k_stream(const typename cplx_of<T>::type* __restrict__ spec, typename cplx_of<T>::type* __restrict__ wspec,
-         const typename cplx_of<T>::type* __restrict__ twg, const T* __restrict__ kv, T sc,
+         const typename cplx_of<T>::type* __restrict__ twg, const T* __restrict__ kv,
          const Ctl* __restrict__ ctl, long long bs) {
   using C = Cfg<T, NN, N>;
   using V = typename C::V;
   constexpr int n = NN, TZ = C::TZ, NT = C::H / TZ;
+  constexpr T ws = T(w_scale<NN>());
   spec = slot_ptr(spec, bs);
   wspec = slot_ptr(wspec, bs);
   twg = slot_ptr(twg, bs);
@@ -487,16 +501,16 @@ k_stream(const typename cplx_of<T>::type* __restrict__ spec, typename cplx_of<T>
   const int ky = tile / NT, kx0 = (tile - ky * NT) * TZ;
   for (int i = threadIdx.x; i < n; i += C::BT) {
     tw[i] = twg[i];
-    kz[i] = -sc * (kv[i] / T(n));
+    kz[i] = -ws * (kv[i] / T(n));
   }
-  T skx[C::VW];
+  T kxs[C::VW];
 #pragma unroll
-  for (int v = 0; v < C::VW; ++v) skx[v] = sc * kv[kx0 + (int(threadIdx.x) * C::VW) % TZ + v];
-  const T sky = sc * kv[ky];
+  for (int v = 0; v < C::VW; ++v) kxs[v] = ws * kv[kx0 + (int(threadIdx.x) * C::VW) % TZ + v];
+  const T kys = ws * kv[ky];
   const size_t off = C::Lay::row(ky) + kx0;
   lds_barrier();
-  if (Q == 0) sweep<C, T, N, 0>(spec + off, wspec + off, pub, tw, kz, skx, sky);
-  else sweep<C, T, N, 1>(spec + off, wspec + off, pub, tw, kz, skx, sky);
+  if (Q == 0) sweep<C, T, N, 0>(spec + off, wspec + off, pub, tw, kz, kxs, kys);
+  else sweep<C, T, N, 1>(spec + off, wspec + off, pub, tw, kz, kxs, kys);
 }
 
 }  // namespace strm
