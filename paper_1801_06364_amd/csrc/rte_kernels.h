@@ -694,6 +694,16 @@ __device__ __forceinline__ double source_weight(const Ctl* __restrict__ ctl, int
   return ctl->qw[r * ctl->qw_cols + stage];
 }
 
+// A stopped step keeps its state: where the new state goes to a buffer of its own
+// (the steps that the reverse sweep recomputes), the workgroup's COUNT elements of
+// the old one are copied there.
+template <int BLOCK, int COUNT, typename T>
+__device__ __forceinline__ void hold_state(const T* u, T* dst) {
+  if (dst == u) return;
+  const size_t o = size_t(blockIdx.x) * COUNT;
+  for (int i = threadIdx.x; i < COUNT; i += BLOCK) dst[o + i] = u[o + i];
+}
+
 // Inverse x transform + epilogue of RB rows per workgroup (grids whose
 // plane does not fit in LDS; the y transform ran before as a pencil pass).
 // Logical order (z group, row block, moment, z in group) so moments sharing
@@ -712,7 +722,10 @@ k_rows_inv(const typename cplx_of<T>::type* spec, const T* vin, T* u, T* dst,
   using V = typename cplx_of<T>::type;
   constexpr int n = NN, H = NN / 2, RB = RowShape<NN>::RB, NB = NN / RB;
   using Lay = RowsLayout<NN, RB>;
-  if (ctl->stop) return;
+  if (ctl->stop) {
+    if constexpr (MODE == EPI_LAST || MODE == EPI_EULER) hold_state<kZBlock, RB * n>(u, dst);
+    return;
+  }
   extern __shared__ __align__(16) unsigned char smem[];
   V* tw = reinterpret_cast<V*>(smem);
   V* pl = tw + n;

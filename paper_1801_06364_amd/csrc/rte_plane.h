@@ -271,7 +271,10 @@ k_plane(const typename cplx_of<T>::type* spec, const T* vin, T* u, T* dst, const
   twg = slot_ptr(twg, bs);
   ctl = slot_ptr(ctl, bs);
   fspec = slot_ptr(fspec, bs);
-  if (ctl->stop) return;
+  if (ctl->stop) {
+    if constexpr (MODE == EPI_LAST || MODE == EPI_EULER) hold_state<C::BT, C::PPW * n * n>(u, dst);
+    return;
+  }
   extern __shared__ __align__(16) unsigned char smem[];
   V* tw = reinterpret_cast<V*>(smem);
   V* pls = tw + n;
