@@ -357,10 +357,11 @@ def gmres_iteration_bytes(n, M, N, s, m, K):
     cycle of m steps. The operator: with K = 0 one application of S + Sigma
     (forward plane pass 2F, streaming pass 2F, inverse pass
     reading the spectrum, input and loss maps and writing the output
-    3F + maps); with K > 0 a copy (2F), K RK4 steps without bookkeeping (per
-    stage 2F + 2F and an inverse pass reading spectrum, stage input, u
-    and maps and writing 1: 4F + maps, the first stage reading u once: one F
-    less) and the difference (3F). Then two classical Gram-Schmidt passes
+    3F + maps); with K > 0 a copy (2F), one forward plane pass (2F), K RK4
+    steps without bookkeeping whose stages hand the spectrum on (per stage
+    the streaming pass 2F and the fused inverse pass 5F + maps: spectrum, stage
+    input and u read, output and its spectrum written; the first stage reads u
+    once: one F less) and the difference (3F). Then two classical Gram-Schmidt passes
     against j + 1 basis vectors (inner products read j + 2 vectors, the
     update reads j + 2 and writes 1), the norm (F) and the normalisation
     (2F)."""
@@ -369,7 +370,7 @@ def gmres_iteration_bytes(n, M, N, s, m, K):
     if K == 0:
         op = 7 * F + maps
     else:
-        op = 2 * F + K * (4 * (8 * F + maps) - F) + 3 * F
+        op = 2 * F + 2 * F + K * (4 * (7 * F + maps) - F) + 3 * F
     tot = 0.0
     for j in range(m):
         tot += op + 2 * ((j + 2) * F + (j + 3) * F) + 3 * F
