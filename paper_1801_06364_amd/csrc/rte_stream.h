@@ -114,10 +114,22 @@ template <typename T, int NN, int N> struct Cfg {
       if (full % w == 0 && w % WPM == 0 && (w >= lo || w == full) && acc_regs(w) <= 168) return w;
     return full;
   }
-  static constexpr int NW = waves(), BT = 64 * NW;
+  static constexpr int NW = waves(), ST = 64 * NW;
+  // Waves of the workgroup. A round is a chain of loads, transforms and barriers,
+  // so a half should not need many: as long as it takes more than eight, waves
+  // that transform only are added to those that sum too. 16^3 P_7 (36 moments,
+  // two to a wave): five rounds instead of nine, step 60 us FP32 and 70 FP64 instead
+  // of 76 and 86 (73 and 85 with a derivative and a coupling pass), of eight solves
+  // together 99 and 121 instead of 111 and 136 (253 and 295).
+  static constexpr int all_waves() {
+    int w = NW;
+    while (w * MPW * 8 < OUT * WPM && w + NW <= 8) w += NW;
+    return w;
+  }
+  static constexpr int TW = all_waves(), BT = 64 * TW;
   static constexpr int PTS = n * TZ;
-  static constexpr int VW = (PTS / BT) % 2 == 0 && sizeof(T) == 4 ? 2 : 1;   // points per 16-byte access
-  static constexpr int PPT = PTS / BT;
+  static constexpr int VW = (PTS / ST) % 2 == 0 && sizeof(T) == 4 ? 2 : 1;   // points per 16-byte access
+  static constexpr int PPT = PTS / ST;
   static constexpr int RK = pl.R[pl.stages - 1];         // last radix of the forward
   static constexpr int PADROWS = n / pl.R[0] > n / RK ? n / pl.R[0] : n / RK;
   static constexpr int DROWS = n + PADROWS;              // exchange buffer
@@ -135,7 +147,7 @@ template <typename T, int NN, int N> struct Cfg {
   // moments per round: one tile for each wave (or part of one), no more than
   // a half has, within 160 KB
   static constexpr int moments() {
-    int m = NW * MPW / WPM;
+    int m = TW * MPW / WPM;
     while (m > MPW && (m - MPW >= OUT || lds_of(m) > 160 * 1024)) m -= MPW;
     return m;
   }
@@ -154,7 +166,7 @@ template <typename T, int NN, int N> struct Cfg {
     const int w = 512 / r;
     return w < 2 ? 2 : (w > 4 ? 4 : w);
   }
-  static_assert(PTS % BT == 0 && BT % TZ == 0 && 64 % TZ == 0, "a thread keeps its kx over its points");
+  static_assert(PTS % ST == 0 && ST % TZ == 0 && 64 % TZ == 0, "a thread keeps its kx over its points");
 };
 
 // Configurations that run this pass: the accumulators, one column's points
@@ -164,8 +176,8 @@ template <typename T, int NN, int N> struct Cfg {
 // 256^3 above P_5.
 template <typename T, int NN, int N> constexpr bool use_stream() {
   using C = Cfg<T, NN, N>;
-  return N <= kDenseOrder && C::NW <= 12 && C::acc_regs(C::NW) <= (C::NW > 8 ? 88 : 168) &&
-         C::lds() <= 160 * 1024 && (C::WPM == 1 || C::MPR * C::WPM == C::NW || N == 0);
+  return N <= kDenseOrder && C::TW <= 12 && C::acc_regs(C::NW) <= (C::TW > 8 ? 88 : 168) &&
+         C::lds() <= 160 * 1024 && (C::WPM == 1 || C::MPR * C::WPM == C::TW || N == 0);
 }
 
 // ------------------------------------------------------------ transforms ---
@@ -301,7 +313,7 @@ __device__ __forceinline__ void load_s(typename C::V (*sv)[C::PPT / C::VW][C::VW
 #pragma unroll
     for (int k = 0; k < C::PPT / C::VW; ++k)
       load_points<C>(sv[I][k], src + (size_t(set_at(N, Q, i)) * C::Lay::MS +
-                                      size_t(k * C::BT * C::VW / C::TZ) * C::Lay::ZS) + lo);
+                                      size_t(k * C::ST * C::VW / C::TZ) * C::Lay::ZS) + lo);
     load_s<C, N, Q, RD, I0, NM, I + 1>(sv, src, lo);
   }
 }
@@ -313,7 +325,7 @@ __device__ __forceinline__ void add_s(typename C::V (*acc)[set_size(N, 1 - Q)][C
   if constexpr (I < NM && I0 + I < C::MPR && i < set_size(N, Q)) {
 #pragma unroll
     for (int k = 0; k < C::PPT / C::VW; ++k)
-      add_moment<C, T, N, set_at(N, Q, i)>(acc[k], sv[I][k], pub + (I0 + I) * C::SLOT + e + k * C::BT * C::VW, kxs, kys);
+      add_moment<C, T, N, set_at(N, Q, i)>(acc[k], sv[I][k], pub + (I0 + I) * C::SLOT + e + k * C::ST * C::VW, kxs, kys);
     // (else the LDS reads of the whole round are hoisted above the sums)
     if constexpr (I % 2 == 1) __builtin_amdgcn_sched_barrier(0);
     add_s<C, T, N, Q, RD, I0, NM, I + 1>(acc, sv, pub, e, kxs, kys);
@@ -335,7 +347,7 @@ __device__ __forceinline__ void add_batches(typename C::V (*acc)[set_size(N, 1 -
       typename C::V s1[1][C::PPT / C::VW][C::VW];
 #pragma unroll
       for (int k = 0; k < C::PPT / C::VW; ++k)
-        load_points<C>(s1[0][k], pub + I0 * C::SLOT + C::DROWS * C::TZ + e + k * C::BT * C::VW);
+        load_points<C>(s1[0][k], pub + I0 * C::SLOT + C::DROWS * C::TZ + e + k * C::ST * C::VW);
       add_s<C, T, N, Q, RD, I0, 1>(acc, s1, pub, e, kxs, kys);
       if constexpr (I0 % 2 == 1) __builtin_amdgcn_sched_barrier(0);
       add_batches<C, T, N, Q, RD, I0 + 1>(acc, sv, src, pub, e, lo, kxs, kys);
@@ -419,10 +431,13 @@ __device__ __forceinline__ void rounds(typename C::V (*acc)[set_size(N, 1 - Q)][
     // (k moves a whole number of rows: uniform base, one lane offset)
     const unsigned lo = unsigned(e / TZ) * unsigned(C::Lay::ZS) + e % TZ;
     V sv[C::SB][C::PPT / C::VW][C::VW];
-    if constexpr (C::SG) load_s<C, N, Q, RD, 0, C::SB>(sv, src, lo);
+    const bool sums = C::TW == C::NW || int(threadIdx.x) < C::ST;   // uniform per wavefront
+    if constexpr (C::SG) {
+      if (sums) load_s<C, N, Q, RD, 0, C::SB>(sv, src, lo);
+    }
     load_tile<C, N, Q, RD + 1>(x, src, g, gl);
     lds_barrier();
-    add_batches<C, T, N, Q, RD, 0>(acc, sv, src, pub, e, lo, kxs, kys);
+    if (sums) add_batches<C, T, N, Q, RD, 0>(acc, sv, src, pub, e, lo, kxs, kys);
     // the sums are formed here (the compiler would sink them to the stores
     // and hold the published values of every round instead)
 #pragma unroll
@@ -455,13 +470,14 @@ __device__ __forceinline__ void sweep(const typename C::V* __restrict__ src, typ
     V x[C::P];
     load_tile<C, N, Q, 0>(x, src, g, tid % C::G);
     rounds<C, T, N, Q, 0>(acc, x, src, pub, tw, kz, kxs, kys, g, tid % C::G);
+    if (C::TW > C::NW && tid >= C::ST) return;
     const int e = tid * C::VW;
     const unsigned lo = unsigned(e / C::TZ) * unsigned(C::Lay::ZS) + e % C::TZ;
 #pragma unroll
     for (int k = 0; k < NI; ++k)
 #pragma unroll
       for (int a = 0; a < OUTQ; ++a) {
-        V* o = dst + (size_t(set_at(N, 1 - Q, a)) * C::Lay::MS + size_t(k * C::BT * C::VW / C::TZ) * C::Lay::ZS) + lo;
+        V* o = dst + (size_t(set_at(N, 1 - Q, a)) * C::Lay::MS + size_t(k * C::ST * C::VW / C::TZ) * C::Lay::ZS) + lo;
         if constexpr (C::VW == 2)
           *reinterpret_cast<float4*>(o) = make_float4(acc[k][a][0].x, acc[k][a][0].y, acc[k][a][1].x, acc[k][a][1].y);
         else *o = acc[k][a][0];
