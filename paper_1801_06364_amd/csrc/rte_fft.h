@@ -1,5 +1,5 @@
 // Device building blocks for the P_N stepper on gfx950: complex helpers,
-// radix-2/3/4/6/8/12/16/24 butterflies and a Stockham auto-sort FFT of compile-time
+// radix-2/3/4/6/8/12/16 butterflies and a Stockham auto-sort FFT of compile-time
 // length executed by a group of P lanes of one wavefront on data staged in
 // LDS.
 //
@@ -197,7 +197,7 @@ template <typename V, int DIR> __device__ __forceinline__ V w24(int t) {
 
 // DFT of R = A B points in registers (A, B coprime or not): r = a + A b,
 // q = c + B d: radix B over b for each a, twiddles exp(DIR 2 pi i a c / R),
-// radix A over a. R divides 24, so every twiddle is a closed form.
+// radix A over a. R (6, 12) divides 24, so every twiddle is a closed form.
 template <typename V, int A, int B, int DIR> __device__ __forceinline__ void dft_ab(V* x) {
   V y[A][B];
 #pragma unroll
@@ -225,9 +225,6 @@ template <typename V, int DIR> struct Bfly<V, 6, DIR> {
 };
 template <typename V, int DIR> struct Bfly<V, 12, DIR> {
   static __device__ __forceinline__ void run(V* v) { dft_ab<V, 3, 4, DIR>(v); }
-};
-template <typename V, int DIR> struct Bfly<V, 24, DIR> {
-  static __device__ __forceinline__ void run(V* v) { dft_ab<V, 3, 8, DIR>(v); }
 };
 
 // Element accessors. An FFT pass addresses element i of FFT f through an

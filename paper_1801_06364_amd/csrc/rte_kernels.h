@@ -461,12 +461,12 @@ k_couple(const typename cplx_of<T>::type* __restrict__ spec, typename cplx_of<T>
 // written once (3F): 64^3 P_21 FP32 289 us for 1.52 GB (5.3 TB/s; 172
 // registers). A pass that gathered each row's inputs by a table, nine reads
 // of every input from beyond L1, took 630 us.
-template <typename V, int N, int LP, int MP, int B, int END>
+template <typename V, int N, int MP, int B, int END>
 struct LoadShellH {
   static __device__ __forceinline__ void run(V* x, const V* __restrict__ sp, const V* __restrict__ dp, size_t ms) {
     if constexpr (B < END) {
       x[B - isqrt_c(B) * isqrt_c(B)] = (m_parity(B) != MP ? sp : dp)[B * ms];
-      LoadShellH<V, N, LP, MP, B + 1, END>::run(x, sp, dp, ms);
+      LoadShellH<V, N, MP, B + 1, END>::run(x, sp, dp, ms);
     }
   }
 };
@@ -519,7 +519,7 @@ template <typename V, typename T, int N, int MP, int L>
 __device__ __forceinline__ void shells_h(V* lo, V* hi, const V* __restrict__ sp, const V* __restrict__ dp,
                                          V* __restrict__ out, size_t ms, T kx, T ky, T sc) {
   if constexpr (L <= N) {
-    if constexpr (L + 1 <= N) LoadShellH<V, N, L & 1, MP, (L + 1) * (L + 1), (L + 2) * (L + 2)>::run(hi, sp, dp, ms);
+    if constexpr (L + 1 <= N) LoadShellH<V, N, MP, (L + 1) * (L + 1), (L + 2) * (L + 2)>::run(hi, sp, dp, ms);
     RowsH<V, T, N, MP, L * L, (L + 1) * (L + 1)>::run(lo, hi, out, ms, kx, ky, sc);
     shells_h<V, T, N, MP, L + 2>(hi, lo, sp, dp, out, ms, kx, ky, sc);
   }
@@ -544,10 +544,10 @@ k_couple_high(const typename cplx_of<T>::type* __restrict__ spec, const typename
   if (cls == 0) shells_h<V, T, N, 0, 0>(a, b, sp, dp, out + pt, MS, kx, ky, sc);
   else if (cls == 1) shells_h<V, T, N, 1, 0>(a, b, sp, dp, out + pt, MS, kx, ky, sc);
   else if (cls == 2) {
-    LoadShellH<V, N, 1, 0, 0, 1>::run(a, sp, dp, MS);
+    LoadShellH<V, N, 0, 0, 1>::run(a, sp, dp, MS);
     shells_h<V, T, N, 0, 1>(a, b, sp, dp, out + pt, MS, kx, ky, sc);
   } else {
-    LoadShellH<V, N, 1, 1, 0, 1>::run(a, sp, dp, MS);
+    LoadShellH<V, N, 1, 0, 1>::run(a, sp, dp, MS);
     shells_h<V, T, N, 1, 1>(a, b, sp, dp, out + pt, MS, kx, ky, sc);
   }
 }
@@ -1764,7 +1764,8 @@ hipError_t prepare_t(const StepArgs& a) {
   }
   if constexpr (strm::use_stream<T, NN, N>())
     set(reinterpret_cast<const void*>(&strm::k_stream<T, NN, N>), strm::Cfg<T, NN, N>::lds());
-  set(reinterpret_cast<const void*>(&k_pencil<T, NN, PENCIL_ZDERIV>), zd_lds<T, NN>());
+  else if constexpr (!pen::use_reg<T, NN, PENCIL_ZDERIV>())
+    set(reinterpret_cast<const void*>(&k_pencil<T, NN, PENCIL_ZDERIV>), zd_lds<T, NN>());
   set(reinterpret_cast<const void*>(&k_pencil<T, NN, PENCIL_ZFWD>), zd_lds<T, NN>());
   set(reinterpret_cast<const void*>(&k_pencil<T, NN, PENCIL_ZINV>), zd_lds<T, NN>());
   if constexpr (N <= kDenseOrder) {
