@@ -146,15 +146,19 @@ struct StepArgs {
   void* v;                  // stage state [M][n^3]
   void* spec;               // xy spectrum [M][n][n][n/2] complex (kx = 0 packs
                             // the real kx = 0 and kx = n/2 columns)
-  void* dspec;              // its z derivative, same layout
-  void* wspec;              // coupled spectrum (orders above kDenseOrder only)
+  void* dspec;              // same layout: the coupled spectrum (streaming pass), or
+                            // the z derivative, which the coupling pass overwrites
+                            // (orders above kDenseOrder: leaves in place)
+  void* wspec;              // coupled spectrum of orders above kDenseOrder
   const void* tw;           // twiddles exp(-2 pi i t / n), n complex
   const void* kv;           // wavenumbers, n
   const void* sig;          // per-degree loss [N+1][n^3]
   const void* q;            // source [M][n^3] or nullptr
   const int* qflag;         // [M][n], per moment and z-plane: source present
   double* phi_int;          // integrated fluence [n^3]
-  double* partial;          // per z-plane fluence-change partial sums [n][2]
+  double* partial;          // fluence-change partial sums, [n][2] per z-plane or (split
+                            // grids) [n n / 16][2] per row block; n^2 pairs allocated, of
+                            // which OP_GROWTH uses kGrowthBlocks values between steps
   double* readings;         // [cap][ndet]
   double* resid;            // [cap]
   const long long* det;     // [ndet]

@@ -86,10 +86,14 @@ __device__ __forceinline__ P* slot_ptr(P* p, long long bs) {
 // plane passes, which then move 2 KB pieces, keep their time if ZG = 8
 // z-planes of a moment run side by side (measured on the 128^3 P_7 FP32
 // pass of the middle stages: 575 us against 648 with ZG = 1, 591 with 2, 572
-// with 16). The streaming pass itself: 333 -> 271 us
-// FP32, 647 -> 525 FP64. Smaller grids sit in the caches, and at 256^3 the
-// two y passes and the row pass lose what the streaming pass gains (per
-// stage 6.14 ms either way): KB = n there.
+// with 16). The streaming pass itself: 333 -> 271 us FP32, 647 -> 525 FP64.
+// Smaller grids sit in the caches up to middle orders, and where they do not (127 to
+// 453 MB at 96^3 P_5 to P_7) the pieces gain nothing: with KB = 4 and 2 96^3 P_7
+// FP32 1480 -> 1451 us a step, FP64 3005 -> 3047, P_5 894 -> 887 and 1822 -> 1825.
+// At 256^3 the y passes lose what the streaming pass gains (P_5 FP32 with KB = 2,
+// addressing free in both: stream 1.62 -> 1.48 ms, y 0.91 + 0.94 -> 0.97 + 0.99, rows
+// 2.56 -> 2.53; steps of P_1 to P_7 -0.5 to +1.6% FP32, -2.4 to +1.8% FP64).
+// KB = n on both.
 template <typename T, int NN> struct SpecLayout {
   static constexpr int H = NN / 2;
   static constexpr int rows_for(int bytes) {   // ky rows per piece of about `bytes`
@@ -459,8 +463,9 @@ k_couple(const typename cplx_of<T>::type* __restrict__ spec, typename cplx_of<T>
 // row shell ahead. W goes to a separate buffer (another class reads the D
 // entries in its place). Bound: HBM, every input read once and every output
 // written once (3F): 64^3 P_21 FP32 289 us for 1.52 GB (5.3 TB/s; 172
-// registers). A pass that gathered each row's inputs by a table, nine reads
-// of every input from beyond L1, took 630 us.
+// registers), FP64 664 us (4.6 TB/s; the shells' 349 registers leave one wave per
+// SIMD). A pass that gathered each row's inputs by a table, nine reads of every
+// input from beyond L1, took 630 and 1292 us.
 template <typename V, int N, int MP, int B, int END>
 struct LoadShellH {
   static __device__ __forceinline__ void run(V* x, const V* __restrict__ sp, const V* __restrict__ dp, size_t ms) {
@@ -707,8 +712,8 @@ __device__ __forceinline__ void hold_state(const T* u, T* dst) {
 // Inverse x transform + epilogue of RB rows per workgroup (grids whose
 // plane does not fit in LDS; the y transform ran before as a pencil pass).
 // Logical order (z group, row block, moment, z in group) so moments sharing
-// loss rows are neighbours on one XCD and neighbouring z write one piece of HBM. FUSE: the output rows, still in LDS, are
-// transformed forward at once (x real-to-complex, as k_rows_fwd) and
+// loss rows are neighbours on one XCD and neighbouring z write one piece of HBM.
+// FUSE: the output rows, still in LDS, are transformed forward at once (x real-to-complex, as k_rows_fwd) and
 // written as the next stage's row spectrum to fspec (which may be the
 // spectrum just read: each workgroup owns its rows), so the next stage
 // needs no separate row pass.

@@ -22,15 +22,18 @@
 //     48^3 P_3 FP32 (eight solves) 57 -> 47 per fused middle pass.
 //
 // The plane sits in LDS with an odd row pitch: the 16 lanes of one LDS cycle
-// touch 16 consecutive columns of a row or one column of 16 rows.
+// touch 16 consecutive columns of a row or one column of 16 rows. The epilogue's
+// items are two consecutive elements per lane (FP32), so its lanes lie two elements
+// apart: 0.62 conflict cycles per LDS instruction of the pass at 128^3 P_7, beside
+// the loads from HBM that it waits for.
 //
 // Bound: HBM (5F + maps per fused middle pass, F = M n^3 elements), 4.6-5.0
 // TB/s where the fields exceed the Infinity Cache and 5.3-6.0 where they do
 // not; skipping every butterfly changes that by 3%. Fused middle pass against
 // the pass with one LDS round trip per Stockham stage that it replaces:
 // 64^3 P_7 FP32 83 -> 60 us (Euler), 48^3 P_3 (eight solves) 111 -> 47, 96^3 P_3
-// 91 -> 52, 48^3 P_4 FP64 47 -> 25, 128^3 P_7 FP64 1363 -> 1145; 128^3 P_7 FP32
-// (a 128-point schedule of its own before) 575 -> 540.
+// 91 -> 53, 48^3 P_4 FP64 47 -> 27, 128^3 P_7 FP64 1363 -> 1145; 128^3 P_7 FP32
+// (a 128-point schedule of its own before) 582 -> 578.
 #pragma once
 
 namespace rte {

@@ -27,9 +27,10 @@
 //
 // Bound: HBM at 128^3 P_7 (without transforms and sums the same sweep takes
 // 230 us); transforms and LDS on the other grids. Against the two passes it
-// replaces: FP32 128^3 P_7 490 -> 275 us, FP64 1003 -> 516, 256^3 P_5 2345 ->
-// 1590, 64^3 P_7 55 -> 28, 64^3 P_5 32 -> 19, 96^3 P_3 47 -> 31, 48^3 P_4 FP64
-// 47 -> 15.
+// replaces: FP32 128^3 P_7 490 -> 285 us, FP64 1003 -> 516, 256^3 P_5 2345 ->
+// 1635, 64^3 P_7 55 -> 30, 64^3 P_5 32 -> 19, 96^3 P_3 47 -> 33, 48^3 P_4 FP64
+// 47 -> 15 (inside a time step, whose field passes take the caches in turn; in a
+// loop of its own 275, 1590, 28 and 31 of these).
 // The transforms of the outputs instead of the inputs (all three terms summed
 // in kz space, one tile per wave) run 2 us faster at 96^3 P_3 and 10% at 256^3,
 // but pass the x and y terms through the z transforms' rounding: the error of
@@ -97,7 +98,7 @@ template <typename T, int NN, int N> struct Cfg {
   static constexpr int OUT = set_size(N, 0) > set_size(N, 1) ? set_size(N, 0) : set_size(N, 1);
   // registers of the accumulators per thread of a workgroup of w waves
   static constexpr int acc_regs(int w) { return OUT * (n * TZ / (64 * w)) * 2 * int(sizeof(T) / 4); }
-  // Waves per workgroup. The largest halves (P_7, 36 moments) run at one point
+  // Waves that sum. The largest halves (P_7, 36 moments) run at one point
   // per thread as far as 12 waves go (96^3 141 us against 161 with two points;
   // at 128^3 the tiles of 16 waves exceed the LDS: 286 against 275 with
   // eight). Otherwise the fewest waves, a divisor of the tile's points, whose
@@ -134,10 +135,15 @@ template <typename T, int NN, int N> struct Cfg {
   static constexpr int PADROWS = n / pl.R[0] > n / RK ? n / pl.R[0] : n / RK;
   static constexpr int DROWS = n + PADROWS;              // exchange buffer
   // S read again from the caches instead of published in LDS: fields below
-  // 120 MB (96^3 P_3 31 us against 39, P_4 47 against 51, P_5 with 127 MB 76
-  // against 73; 96^3 P_3 FP64 54 against 74, 48^3 P_4 FP64 15 against 24), but
-  // not at 64^3, whose tiles leave room for enough workgroups either way (P_7
-  // 30 against 28)
+  // 120 MB, which leaves LDS for more workgroups per CU (96^3 P_3 31 us against 39,
+  // P_4 47 against 51, P_5 with 127 MB 76 against 73; 96^3 P_3 FP64 54 against 74,
+  // 48^3 P_4 FP64 15 against 24). Not at 64^3, where two workgroups of eight
+  // wavefronts fit with S in LDS too (FP64 P_6, P_7: one): reading again costs steps
+  // of P_2 to P_7 0 to 5.5%, FP32 and FP64, and those of eight solves together 0 to 9%.
+  // The size is one solve's, also where a batch's slots exceed the caches, since
+  // a slot computes what a solve alone does: eight slots gain 3 to 17% from it in
+  // FP64 (32^3 to 128^3) and at 48^3 P_3, P_4, and lose 2 to 5% in FP32 at 32^3 P_4 and
+  // up, 48^3 P_5 and up, 96^3 P_3, P_4 and 128^3 P_1, P_2.
   static constexpr bool SG =
       n != 64 && size_t(N + 1) * (N + 1) * n * n * n * sizeof(T) < size_t(120) * 1000 * 1000;
   static constexpr int SLOT = ((SG ? 0 : n) + DROWS) * TZ;   // LDS of one moment: S (if published), derivative
@@ -381,7 +387,7 @@ __device__ __forceinline__ void load_tile(typename C::V* x, const typename C::V*
   const int i = RD * C::MPR + g;
   if (g < C::MPR && i < set_size(N, Q)) {
     const typename C::V* s = src + set_offset<C>(Q, i);
-    asm volatile("" : "+v"(gl));   // (see `inputs`)
+    asm volatile("" : "+v"(gl));   // (offsets formed anew in every round, see `rounds`)
     const unsigned lo = unsigned(gl / C::TZ) * unsigned(AX) + gl % C::TZ;
 #pragma unroll
     for (int t = 0; t < C::P / R0; ++t)
